@@ -60,17 +60,17 @@ typedef enum {
   PD_FP32 = 1,     /* precision form: FP32 state and rotations; FP64 time, field table,
                       rotation angles, projection and density sum; the state is
                       renormalised every 1024 absolute steps (the exact step is unitary,
-                      Sec. III); every rotation rounds each state component once */
-  PD_FP32_FAST = 2 /* as PD_FP32, but the Strang rotations are plain shears (one
-                      component rounded twice per rotation) whose orientation alternates
-                      from one stage to the next, so that the doubly rounded component
-                      alternates, and a stage's two rotations in one plane (field part
-                      and per-point part) run as five shears: a quarter fewer
-                      instructions.  On the 2048^2 benchmark solve every point is within
-                      1e-5 of FP64 (worst 9.3e-6, PD_FP32 9.6e-6); over long solves on
-                      wide grids its worst points reach up to about 1.8x PD_FP32's, so it
-                      is not held to PD_FP32's bound (the midpoint schemes run as
-                      PD_FP32) */
+                      Sec. III).  Strang: the rotations about x round each state component
+                      once, those about y are plain shears (one component rounded twice)
+                      whose orientation alternates from one stage to the next; grids of
+                      fewer than 32 rows, and steps too large for one rotation about x
+                      (pd_info.rotation_form), round each component once in every rotation */
+  PD_FP32_FAST = 2 /* as PD_FP32, but every Strang rotation is plain shears, of alternating
+                      orientation: 6 instructions for a point's step instead of 7.  On the
+                      2048^2 benchmark solve every point is within 1e-5 of FP64 in both
+                      forms; over long solves on wide grids the worst points of this one are
+                      further off than PD_FP32's, so it is not held to PD_FP32's bound (the
+                      midpoint schemes run as PD_FP32) */
 } pd_precision;
 
 typedef enum {
@@ -150,7 +150,7 @@ typedef struct {
   double A_min, A_max;      /* range of A over the midpoints and the end points */
   int precision;            /* pd_precision */
   int scheme;               /* pd_scheme */
-  int points_per_lane;      /* launch shape in use */
+  int points_per_lane;      /* launch shape in use: as set, or chosen by the library (then up to 8) */
   int block_threads;
   int table_stage;          /* 1 = LDS chunks, 2 = scalar-unit reads */
   int chunk_steps;
@@ -325,7 +325,9 @@ pd_status pd_load_state(pd_grid g, const void* host, size_t bytes, long long ste
    a power of two in [64, 4096] (at most 1024 in the FP32 form, whose
    renormalisation period it must divide); a solve whose chunk of rows would
    exceed 64 KiB of LDS (long rows: fourth order, y component) reads them with the
-   scalar unit instead.  0 keeps the current value.  Results do not depend on the
+   scalar unit instead.  A Strang solve of at least 32 rows keeps coefficients of its own
+   in the LDS whatever the stage and the chunk; its points per lane, if never set, follow
+   the grid's size.  0 keeps the current value.  Results do not depend on the
    launch shape (bit for bit). */
 pd_status pd_set_launch(pd_grid g, int points_per_lane, int block_threads, int table_stage, int chunk_steps);
 
@@ -337,7 +339,8 @@ void pd_destroy_grid(pd_grid g);
 /* Choose the launch shape of g by timing candidates on the first
    min(trial_steps, N) steps of g's own solve on `stream`: points_per_lane
    {1, 2, 4} x block_threads {64, 256} x (scalar-unit rows, LDS chunks of 256 or
-   1024 steps for Strang).  The fastest is applied as by pd_set_launch; the solve
+   1024 steps for Strang), or, for a Strang solve of at least 32 rows,
+   points_per_lane {1, 2, 4, 8} x block_threads {64, 256}.  The fastest is applied as by pd_set_launch; the solve
    is left rewound (steps_done = 0).  With use_cache != 0 and the environment
    variable PD_AUTOTUNE_CACHE naming a file, a shape stored there for the same
    (GPU architecture, precision, scheme, rotation form, floor(log2 points)) is

@@ -44,8 +44,10 @@ std::string cache_key(pd_grid g) {
   std::ostringstream k;
   static const char* const kSchemes[] = {"strang", "midpoint", "strang4", "midpoint4"};
   static const char* const kPrecisions[] = {"fp64", "fp32", "fp32fast"};
+  // form 2: Strang by columns (one entry per series order would time the same kernel again)
+  const int form = g->series ? 2 : g->form;
   k << arch_name(g->device) << " " << kPrecisions[g->precision] << " " << kSchemes[g->scheme]
-    << (g->field.elliptic ? "-xy" : "") << " " << g->form << " " << size_class;
+    << (g->field.elliptic ? "-xy" : "") << " " << form << " " << size_class;
   return k.str();
 }
 
@@ -65,6 +67,17 @@ bool cache_lookup(const std::string& key, Shape* out) {
     }
   }
   return found;
+}
+
+// pd_set_launch, and the column kernels' eight points per lane, which it does not offer.
+pd_status apply(pd_grid g, const Shape& s) {
+  const bool eight = s.ppl == 8 && g->series;
+  const pd_status r = pd_set_launch(g, eight ? 0 : s.ppl, s.block, s.stage, s.chunk);
+  if (r == PD_OK && eight) {
+    g->points_per_lane = 8;
+    g->points_chosen = true;
+  }
+  return r;
 }
 
 // One line per store, written by a single append-mode write so that lines stored at the
@@ -125,22 +138,25 @@ pd_status pd_autotune(pd_grid g, long long trial_steps, int use_cache, void* str
   const std::string key = cache_key(g);
   Shape best{};
   if (use_cache && cache_lookup(key, &best)) {
-    pd_status s = pd_set_launch(g, best.ppl, best.block, best.stage, best.chunk);
+    pd_status s = apply(g, best);
     if (s == PD_OK) g->steps_done = 0;
     return s;
   }
   std::vector<Shape> cands;
-  for (int ppl : {1, 2, 4})
+  for (int ppl : {1, 2, 4, 8}) {
+    if (ppl == 8 && !g->series) continue;
     for (int block : {64, 256}) {
       cands.push_back({ppl, block, 2, g->chunk_steps});
-      if (base_scheme(g->scheme) == PD_SCHEME_STRANG)
+      // the column kernels keep their coefficients in the LDS whatever the stage says
+      if (base_scheme(g->scheme) == PD_SCHEME_STRANG && !g->series)
         for (int chunk : {256, 1024}) cands.push_back({ppl, block, 1, chunk});
     }
+  }
   const long long steps = trial_steps < g->field.n_steps ? trial_steps : g->field.n_steps;
   hipStream_t st = static_cast<hipStream_t>(stream);
   float best_ms = 1e30f;
   for (const Shape& c : cands) {
-    pd_status s = pd_set_launch(g, c.ppl, c.block, c.stage, c.chunk);
+    pd_status s = apply(g, c);
     if (s != PD_OK) return s;
     float ms = 0;
     s = time_best(
@@ -156,7 +172,7 @@ pd_status pd_autotune(pd_grid g, long long trial_steps, int use_cache, void* str
     }
   }
   g->steps_done = 0;
-  pd_status s = pd_set_launch(g, best.ppl, best.block, best.stage, best.chunk);
+  pd_status s = apply(g, best);
   if (s == PD_OK && use_cache) cache_store(key, best, best_ms);
   return s;
 }

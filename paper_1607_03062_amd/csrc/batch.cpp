@@ -15,7 +15,7 @@
 using namespace pdx;
 
 // Device descriptors of one launch sequence in one allocation that one copy fills:
-// the work counter, the solves, the work items and the density jobs, each at a
+// the work counters, the solves, the work items and the density jobs, each at a
 // 256-byte boundary; and one rho per member.
 struct BatchDescriptors {
   unsigned char* d_block = nullptr;
@@ -63,9 +63,9 @@ struct pd_batch_s {
   int n_items_last = 0;
   int n_separate_last = 0;
 
-  // blocks of the persistent kernel resident at once (its launch size) for the launch
+  // blocks of each persistent kernel resident at once (its launch size) for the launch
   // shape slots_ppl x slots_block
-  long long slots = 0;
+  long long slots[kBatchKinds] = {};
   int slots_ppl = 0, slots_block = 0;
 };
 
@@ -125,29 +125,32 @@ bool graph_current(pd_batch b) {
 
 struct Plan {
   std::vector<BatchSolve> solves;
-  std::vector<BatchItem> items;
+  std::vector<BatchItem> items;  // those of kBatchRows, then those of kBatchColumns
+  size_t kind_items[kBatchKinds] = {};
   std::vector<DensityJob> jobs;
   std::vector<std::pair<size_t, SolveParams>> separate;  // members run by their own launch
   long long density_tiles = 0;
 };
 
-// Blocks of the persistent kernel resident on the device at once for the batch's
-// launch shape: the number it is launched with (at most one per work item).
-long long persistent_slots(pd_batch b) {
-  if (b->slots <= 0 || b->slots_ppl != b->points_per_lane || b->slots_block != b->block_threads) {
-    const int per_cu = batch_blocks_per_cu(b->points_per_lane, b->block_threads);
+int batch_kind(pd_grid g) { return g->series ? kBatchColumns : kBatchRows; }
+
+// Blocks of a persistent kernel resident on the device at once for the batch's launch
+// shape: the number it is launched with (at most one per work item).
+long long persistent_slots(pd_batch b, int kind) {
+  if (b->slots_ppl != b->points_per_lane || b->slots_block != b->block_threads) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess || cus <= 0)
       cus = 1;
-    b->slots = (long long)cus * per_cu;
+    for (int k = 0; k < kBatchKinds; ++k)
+      b->slots[k] = (long long)cus * batch_blocks_per_cu(k, b->points_per_lane, b->block_threads);
     b->slots_ppl = b->points_per_lane;
     b->slots_block = b->block_threads;
   }
-  return b->slots;
+  return b->slots[kind];
 }
 
-// Members the persistent kernel runs: second-order Strang, no y component, with
-// fewer tiles than it has resident blocks.  A member with at least that many tiles
+// Members the persistent kernels run: second-order Strang, no y component, with
+// fewer tiles than the kernel has resident blocks.  A member with at least that many tiles
 // fills the device by itself; its own launch (its grid's shape, blocks scheduled by
 // the hardware) then runs at the rate of the solve alone, where the persistent
 // kernel's equal items would leave a partly filled last round of blocks (a lone
@@ -155,8 +158,8 @@ long long persistent_slots(pd_batch b) {
 // own launch).
 bool persistent_member(pd_batch b, pd_grid g) {
   if (g->scheme != PD_SCHEME_STRANG || g->field.elliptic) return false;
-  const long long tile = (long long)b->block_threads * b->points_per_lane;
-  return (g->grid.points() + tile - 1) / tile < persistent_slots(b);
+  long long span;
+  return g->batch_tiles(b->points_per_lane, b->block_threads, &span) < persistent_slots(b, batch_kind(g));
 }
 
 // Descriptors for advancing member i over steps [begin[i], end[i]) (no work
@@ -176,6 +179,7 @@ pd_status make_plan(pd_batch b, double* rho_copies, const std::vector<long long>
     }
     plan->solves[i].p = g->solve_params(begin[i], end[i], st);
     plan->solves[i].p.stage = 0;  // the persistent kernel reads field rows with the scalar unit
+    if (g->series) plan->solves[i].p.columns = g->columns(b->points_per_lane, false);
     plan->solves[i].precision = g->precision;
     plan->solves[i].form = g->form;
     if (begin[i] < end[i]) {
@@ -188,11 +192,16 @@ pd_status make_plan(pd_batch b, double* rho_copies, const std::vector<long long>
   // Longest first: every tile of a solve costs (end - begin) steps per point.
   std::stable_sort(order.begin(), order.end(),
                    [&](size_t a, size_t c) { return end[a] - begin[a] > end[c] - begin[c]; });
-  const long long tile = (long long)b->block_threads * b->points_per_lane;
   plan->items.clear();
-  for (size_t i : order) {
-    long long npts = b->grids[i]->grid.points();
-    for (long long base = 0; base < npts; base += tile) plan->items.push_back(BatchItem{(int)i, 0, base});
+  for (int kind = 0; kind < kBatchKinds; ++kind) {
+    const size_t before = plan->items.size();
+    for (size_t i : order) {
+      if (batch_kind(b->grids[i]) != kind) continue;
+      long long span;
+      const long long tiles = b->grids[i]->batch_tiles(b->points_per_lane, b->block_threads, &span);
+      for (long long q = 0; q < tiles; ++q) plan->items.push_back(BatchItem{(int)i, 0, q * span});
+    }
+    plan->kind_items[kind] = plan->items.size() - before;
   }
   if (plan->items.size() > (size_t)0x7fffffff) return set_error(PD_ERR_INVALID, "too many work items");
   plan->jobs.clear();
@@ -242,7 +251,7 @@ pd_status upload(pd_batch b, BatchDescriptors& D, const Plan& plan, hipStream_t 
   return PD_OK;
 }
 
-// Enqueue one launch sequence on `stream`: the persistent kernel over the plan's
+// Enqueue one launch sequence on `stream`: the persistent kernels over the plan's
 // items and, concurrently on the side stream (forked from and joined back into
 // `stream` with events, so the sequence stays one stream-ordered unit and one
 // captured graph), the other members' own launches; then the batched density.
@@ -250,21 +259,27 @@ pd_status upload(pd_batch b, BatchDescriptors& D, const Plan& plan, hipStream_t 
 // leave as its queue drains.
 pd_status enqueue(pd_batch b, BatchDescriptors& D, const Plan& plan, hipStream_t stream) {
   hipError_t e;
-  const bool fork = !plan.separate.empty();
+  const size_t* n = plan.kind_items;
+  const bool both = n[kBatchRows] && n[kBatchColumns];  // the row tiles then go beside, too
+  const bool fork = both || !plan.separate.empty();
+  if (!plan.items.empty() && (e = launch_batch_reset(D.d_counter, stream)) != hipSuccess)
+    return hip_error(e, "batch launch");
   if (fork) {
     if ((e = hipEventRecord(b->fork, stream)) != hipSuccess) return hip_error(e, "hipEventRecord(fork)");
     if ((e = hipStreamWaitEvent(b->side_stream, b->fork, 0)) != hipSuccess) return hip_error(e, "hipStreamWaitEvent");
   }
-  if (!plan.items.empty()) {
-    long long blocks = std::min<long long>(persistent_slots(b), (long long)plan.items.size());
-    e = launch_batch(b->points_per_lane, b->block_threads, (int)blocks, D.d_solves, D.d_items,
-                     (int)plan.items.size(), D.d_counter, stream);
+  for (int kind = 0; kind < kBatchKinds; ++kind) {
+    if (!n[kind]) continue;
+    const BatchItem* items = D.d_items + (kind == kBatchColumns ? n[kBatchRows] : 0);
+    const long long blocks = std::min<long long>(persistent_slots(b, kind), (long long)n[kind]);
+    e = launch_batch(kind, b->points_per_lane, b->block_threads, (int)blocks, D.d_solves, items, (int)n[kind],
+                     D.d_counter + kind, both && kind == kBatchRows ? b->side_stream : stream);
     if (e != hipSuccess) return hip_error(e, "batch launch");
   }
   // the other members: the single-solve kernels, exactly as a solve alone
   for (const auto& m : plan.separate) {
     pd_grid g = b->grids[m.first];
-    e = launch_propagate(g->scheme, g->precision, g->points_per_lane, g->block_threads, g->taylor,
+    e = launch_propagate(g->scheme, g->precision, g->shape_points(), g->block_threads, g->taylor,
                          g->field.elliptic ? 1 : 0, m.second, b->side_stream);
     if (e != hipSuccess) return hip_error(e, "member launch");
   }

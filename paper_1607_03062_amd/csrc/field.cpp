@@ -336,15 +336,43 @@ void put(std::vector<unsigned char>* bytes, size_t offset, size_t index, double 
 
 }  // namespace
 
-void build_step_table(const FieldTables& t, int scheme, int precision, int form, double vsign,
+void build_step_table(const FieldTables& t, int scheme, int precision, int form, bool columns, double vsign,
                       std::vector<unsigned char>* rows) {
   const long long N = t.n_steps;
   const int S = t.comp.stages;
   const int ell = t.elliptic ? 1 : 0;
   const size_t W = table_row_values(scheme, ell);
   const long long R = table_rows(scheme, ell, N);
-  rows->assign((size_t)R * table_row_bytes(scheme, precision, ell), 0);
   const double* c = t.comp.c;
+  // The y half steps of neighbouring stages (and of the last stage of a step and
+  // the first of the next) are merged; the field part of the merged rotation
+  // after stage j has half angle dt (c_j A_y,j + c_j+1 A_y,j+1) / 2.
+  auto y_half = [&](long long k, int j) {
+    auto ay = [&](long long kk, int jj) { return t.Ay_mid[(size_t)kk * S + jj]; };
+    double sum;
+    if (j + 1 < S)
+      sum = c[j] * ay(k, j) + c[j + 1] * ay(k, j + 1);
+    else if (k + 1 < N)
+      sum = c[j] * ay(k, j) + c[0] * ay(k + 1, 0);
+    else
+      sum = c[j] * ay(k, j);  // closing half step
+    return vsign * 0.5 * t.dt * sum;
+  };
+  const double open = ell ? vsign * 0.5 * t.dt * (c[0] * t.Ay_mid[0]) : 0.0;  // opening half step
+  if (columns) {
+    // half angles in FP64: per stage c_j dt A_x, then those of the y rotations' field parts
+    const size_t V = (size_t)S * (ell ? 2 : 1);
+    rows->assign((size_t)R * V * sizeof(double), 0);
+    double* d = reinterpret_cast<double*>(rows->data());
+    for (long long k = 0; k < N; ++k)
+      for (int j = 0; j < S; ++j) {
+        d[(size_t)k * V + j] = vsign * (c[j] * t.dt) * t.A_mid[(size_t)k * S + j];
+        if (ell) d[(size_t)k * V + S + j] = y_half(k, j);
+      }
+    if (ell) d[(size_t)N * V + S] = open;
+    return;
+  }
+  rows->assign((size_t)R * table_row_bytes(scheme, precision, ell), 0);
   if (base_scheme(scheme) == PD_SCHEME_MIDPOINT) {
     // per stage the phase increment c_j dt A at the stage midpoint (then c_j dt A_y)
     double* d = reinterpret_cast<double*>(rows->data());
@@ -371,22 +399,9 @@ void build_step_table(const FieldTables& t, int scheme, int precision, int form,
   for (long long k = 0; k < N; ++k)
     for (int j = 0; j < S; ++j) store(k, (size_t)j, vsign * (c[j] * t.dt) * t.A_mid[(size_t)k * S + j]);
   if (!ell) return;
-  // The y half steps of neighbouring stages (and of the last stage of a step and
-  // the first of the next) are merged; the field part of the merged rotation
-  // after stage j has half angle dt (c_j A_y,j + c_j+1 A_y,j+1) / 2.
-  auto ay = [&](long long k, int j) { return t.Ay_mid[(size_t)k * S + j]; };
   for (long long k = 0; k < N; ++k)
-    for (int j = 0; j < S; ++j) {
-      double sum;
-      if (j + 1 < S)
-        sum = c[j] * ay(k, j) + c[j + 1] * ay(k, j + 1);
-      else if (k + 1 < N)
-        sum = c[j] * ay(k, j) + c[0] * ay(k + 1, 0);
-      else
-        sum = c[j] * ay(k, j);  // closing half step
-      store(k, (size_t)(S + j), vsign * 0.5 * t.dt * sum);
-    }
-  store(N, (size_t)S, vsign * 0.5 * t.dt * (c[0] * ay(0, 0)));  // opening half step
+    for (int j = 0; j < S; ++j) store(k, (size_t)(S + j), y_half(k, j));
+  store(N, (size_t)S, open);
 }
 
 size_t point_coefficient_pairs_x(int scheme, int precision) {
@@ -425,15 +440,16 @@ void dither(double x, int phases, float* out) {
 
 }  // namespace
 
-void build_point_coefficients(const Grid& g, const FieldTables& t, int scheme, int precision, int form, double vsign,
-                              std::vector<unsigned char>* bytes, size_t* col_offset, size_t* row_offset) {
+void build_point_coefficients(const Grid& g, const FieldTables& t, int scheme, int precision, int form, bool columns,
+                              double vsign, std::vector<unsigned char>* bytes, size_t* col_offset,
+                              size_t* row_offset) {
   const bool f32 = is_fp32(precision);
   const size_t v = f32 ? sizeof(float) : sizeof(double);
   const int H = coefficient_phases(precision);
   const size_t nxp = point_coefficient_pairs_x(scheme, precision), nyp = point_coefficient_pairs_y(scheme, precision);
   auto align = [](size_t n) { return (n + 255) / 256 * 256; };
   *col_offset = align(bytes->size());
-  *row_offset = align(*col_offset + 2 * nxp * v * (size_t)g.nx);
+  *row_offset = align(*col_offset + (columns ? 0 : 2 * nxp * v * (size_t)g.nx));
   bytes->resize(align(*row_offset + 2 * nyp * v * (size_t)g.ny));
   // pair `pair` of `entry` (column or row) from the exact coefficients (a, s): one
   // value per phase in FP32 (dithered), the value itself in FP64
@@ -476,7 +492,7 @@ void build_point_coefficients(const Grid& g, const FieldTables& t, int scheme, i
     nmx = nmy = 1;
   }
   double a, s;
-  for (int i = 0; i < g.nx; ++i)
+  for (int i = 0; i < (columns ? 0 : g.nx); ++i)
     for (int q = 0; q < nmx; ++q) {
       rotation_coefficients(vsign * (mx[q] * t.dt) * g.px(i), form, &a, &s);
       store_pair(*col_offset, (size_t)i, nxp, (size_t)q * H, H, a, s);
@@ -501,6 +517,66 @@ int strang_form(const Grid& g, const FieldTables& t) {
   double pymax = std::fmax(std::fabs(g.py(0)), std::fabs(g.py(g.ny - 1)));
   double phi = 2.0 * t.comp.cmax * t.dt * std::fmax(std::fmax(amax, aymax), std::fmax(pxmax, pymax));
   return phi <= kShearMaxAngle ? kFormShear : kFormVersine;
+}
+
+int column_series(const Grid& g, const FieldTables& t, int precision) {
+  if (g.ny < kColumnMinRows || strang_form(g, t) != kFormShear) return 0;
+  // half angles of a stage: c dt (px + A_x), and at most c dt |A_y| for the field part of a
+  // y rotation
+  const double aymax = std::fmax(std::fabs(t.Ay_min), std::fabs(t.Ay_max));
+  const double h = t.comp.cmax * t.dt * std::fmax(t.E_max, aymax);
+  if (!(h <= 0.25 * kPi)) return 0;
+  const double x = h * h, r = 4.0 * x / (kPi * kPi);
+  // the omitted terms, relative to the leading one: tan as in taylor_order; sin(2h)
+  // alternates, so at most its first.  FP32: small against the dithering's 1/8 of a spacing.
+  const double tol = is_fp32(precision) ? 0x1p-30 : 0x1p-56;
+  for (int J : {3, 5, 8, 12, 16, 20, 24}) {
+    const double e = tan_series_coef(J + 1) * std::pow(x, J) / (1.0 - r);
+    if (e <= tol && std::fabs(sin2_series_coef(J + 1)) * std::pow(x, J) <= tol) return J;
+  }
+  return kSeriesMax;
+}
+
+int column_points_per_lane(const Grid& g, int precision, int elliptic) {
+  // More points per lane: fewer LDS reads and coefficients for a point's step, as long as
+  // every SIMD keeps a wave (FP64, whose FMAs a wave with a few points issues without gaps),
+  // or two (FP32: two waves' FMAs issue together).  The device has 1024 SIMDs.
+  const long long waves = is_fp32(precision) ? 2048 : 1024;
+  // eight points with a y component in FP32 take more than half of the registers
+  for (int ppl = is_fp32(precision) && elliptic ? 4 : 8; ppl > 1; ppl /= 2)
+    if (g.points() >= 64 * ppl * waves) return ppl;
+  return 1;
+}
+
+ColumnGeometry column_geometry(const Grid& g, int precision, int stages, int elliptic, int points_per_lane,
+                               bool alone) {
+  const int pair = is_fp32(precision) ? 8 : 16;
+  const long long bands = (g.ny + points_per_lane - 1) / points_per_lane;
+  ColumnGeometry best{};
+  double best_cost = 0.0;
+  // Fewer columns to a wave: fewer coefficients to evaluate; more: fewer lanes without a
+  // row where the bands do not fill 64 lanes.  In units of a point's step (6 FMAs, at half
+  // the rate in FP64) a column's coefficients and reads take a wave about 1/4 (FP32) or 1/8.
+  // A solve alone on the device, up to one wave a SIMD: lanes without a row cost nothing, so
+  // one column (200^2 FP64, 8000 steps, two points a lane: 0.28 ms, 0.35 with four columns).
+  for (int s = 0; s <= (stages == 5 ? 3 : 4); ++s) {
+    const int lanes = 64 >> s;
+    ColumnGeometry c{};
+    c.cshift = s;
+    c.segs = (int)((bands + lanes - 1) / lanes);
+    const long long supers = (g.nx + (1 << kColumnSuperShift) - 1) >> kColumnSuperShift;
+    c.units = (int)((supers * c.segs) << (kColumnSuperShift - s));
+    const int spaces = (1 << s) + (elliptic ? 1 : 0);  // columns of coefficients in the LDS
+    c.chunk = std::min(kColumnEntries, kColumnPairBytes / pair / spaces) / stages / 4 * 4;
+    const double waves = (double)c.segs * (double)((g.nx + (1 << s) - 1) >> s);
+    const double cost = waves * (points_per_lane + spaces * (is_fp32(precision) ? 1.0 / 4 : 1.0 / 8));
+    if (best.units == 0 || cost < best_cost) {
+      best = c;
+      best_cost = cost;
+    }
+    if (s == 0 && alone && waves <= 1024.0) break;
+  }
+  return best;
 }
 
 int taylor_order(double x_max, int precision, int form) {

@@ -6,6 +6,9 @@
 // for every lane: it is either staged through LDS in time chunks (every lane then
 // reads it into VGPRs) or read by the scalar unit into SGPRs.
 //
+// Most Strang solves run by columns (strang_columns.h); the Strang kernel of this file takes
+// grids of fewer than 32 rows and the steps too large for that.
+//
 // Strang scheme (Sec. III, Eqs. (11)-(12), with the midpoint Hamiltonian
 // sigma_x P_x + sigma_y p_y split into its two parts):
 //   U_k = exp(-i dt py sy / 2) exp(-i dt (px + A_k) sx) exp(-i dt py sy / 2).
@@ -50,174 +53,11 @@
 #include <mutex>
 
 #include "pd_internal.h"
+#include "rotations.h"
+#include "strang_columns.h"
 
 namespace pdx {
 namespace {
-
-// Rotation of (u, v) by phi: u' = u cos - v sin, v' = u sin + v cos.
-// Shear form, t = tan(phi/2), s = sin(phi): u -= t v; v += s u; u -= t v.
-template <typename R>
-__device__ __forceinline__ void rotate_shear(R& u, R& v, R t, R s) {
-  u = fma(-t, v, u);
-  v = fma(s, u, v);
-  u = fma(-t, v, u);
-}
-
-// Versine form, h = cos - 1: u' = u + h u - s v,  v' = v + h v + s u.
-__device__ __forceinline__ void rotate_versine(double& u, double& v, double h, double s) {
-  double nu = fma(h, u, fma(-s, v, u));
-  double nv = fma(h, v, fma(s, u, v));
-  u = nu;
-  v = nv;
-}
-
-// FP32 versine form: the small increment is formed first and added once, so the
-// state sees a single rounding per component per rotation.
-__device__ __forceinline__ void rotate_versine(float& u, float& v, float h, float s) {
-  float du = fmaf(h, u, -(s * v));
-  float dv = fmaf(h, v, s * u);
-  u = u + du;
-  v = v + dv;
-}
-
-template <int FORM, typename R>
-__device__ __forceinline__ void rotate(R& u, R& v, R a, R s) {
-  if (FORM == kFormShear)
-    rotate_shear(u, v, a, s);
-  else
-    rotate_versine(u, v, a, s);
-}
-
-
-// Shear form with every component rounded once per rotation: the two u shears
-// add up to u - t (v + v'), so u is updated from its value before the rotation
-// (3 FMA + 1 add).  In FP32 the state's rounding errors are the whole error of a
-// solve, and the second rounding of u per rotation dominates them (its increments
-// are small, and the roundings of a slowly varying state accumulate); rounding each
-// component once halves the worst-point error of the FP32 form on the benchmark
-// workloads, for a quarter more instructions.
-__device__ __forceinline__ void rotate_shear_once(float& u, float& v, float t, float s) {
-  float u1 = fmaf(-t, v, u);
-  float v1 = fmaf(s, u1, v);
-  float w = v + v1;
-  u = fmaf(-t, w, u);
-  v = v1;
-}
-
-// The same shear rotation with the roles of u and v exchanged: v += t u; u -= s v;
-// v += t u.  Now v is the component rounded twice.
-template <typename R>
-__device__ __forceinline__ void rotate_shear_vu(R& u, R& v, R t, R s) {
-  v = fma(t, u, v);
-  u = fma(-s, v, u);
-  v = fma(t, u, v);
-}
-
-// Two rotations in one plane, by a and then by b, as five shears: the last shear of
-// the first triple and the first of the second act on the same component, so they
-// merge into one with the summed coefficient (one add).  Both orientations.
-template <typename R>
-__device__ __forceinline__ void rotate_two_shear(R& u, R& v, R ta, R sa, R tb, R sb) {
-  u = fma(-ta, v, u);
-  v = fma(sa, u, v);
-  u = fma(-(ta + tb), v, u);
-  v = fma(sb, u, v);
-  u = fma(-tb, v, u);
-}
-
-template <typename R>
-__device__ __forceinline__ void rotate_two_shear_vu(R& u, R& v, R ta, R sa, R tb, R sb) {
-  v = fma(ta, u, v);
-  u = fma(-sa, v, u);
-  v = fma(ta + tb, u, v);
-  u = fma(-sb, v, u);
-  v = fma(tb, u, v);
-}
-
-// Shear variants (FP32 forms):
-//   kShearPlain  u -= t v; v += s u; u -= t v (u rounded twice per rotation);
-//   kShearOnce   each component rounded once (rotate_shear_once, 4 instructions);
-//   kShearAlt    plain shears with the orientation alternating from one stage to the
-//                next (u-v-u, then v-u-v; the parity of the absolute stage index), so
-//                that the doubly rounded component alternates and the systematic part
-//                of the roundings largely cancels between neighbouring stages; the
-//                stage's two rotations in one plane (field and per-point parts) run as
-//                five shears (rotate_two_shear), which rounds less for the same count:
-//                3 instructions per rotation.
-constexpr int kShearPlain = 0;
-constexpr int kShearOnce = 1;
-constexpr int kShearAlt = 2;
-
-// A rotation in the solve's form and shear variant SH; odd: the stage's parity
-// (kShearAlt only; a compile-time constant wherever the steps are unrolled).
-template <int FORM, int SH, typename R>
-__device__ __forceinline__ void rot(R& u, R& v, R a, R s, bool odd = false) {
-  if constexpr (FORM == kFormShear && SH == kShearOnce && sizeof(R) == 4) {
-    rotate_shear_once(u, v, a, s);
-  } else if constexpr (FORM == kFormShear && SH == kShearAlt) {
-    if (odd)
-      rotate_shear_vu(u, v, a, s);
-    else
-      rotate_shear(u, v, a, s);
-  } else {
-    rotate<FORM>(u, v, a, s);
-  }
-}
-
-struct PointCoords {
-  int i, j;
-  double px, py;
-};
-
-__device__ __forceinline__ PointCoords coords(const SolveParams& p, long long idx) {
-  long long j = idx / p.nx;
-  long long i = idx - j * p.nx;
-  PointCoords c;
-  c.i = (int)i;
-  c.j = (int)j;
-  c.px = p.px_min + (double)i * p.dx;
-  c.py = p.py_min + (double)j * p.dy;
-  return c;
-}
-
-// Rotation layout of one step of a composition with NS stages.  Stage j applies
-// the x rotation by its field part (table) and by its per-point part (class
-// xcls(j) of the column coefficients), then the y rotation that follows it: its
-// per-point part (class ycls(j) of the row coefficients) and, with a y component
-// of the field (POL), its field part (table).  The y rotations of neighbouring
-// stages, and of the last stage of a step and the first of the next, are merged;
-// the solve opens and closes with a half step (the last row class).
-template <int NS>
-struct Layout;
-template <>
-struct Layout<1> {
-  static constexpr int NX = 1, NY = 2;  // y classes: full, half
-  __device__ static constexpr int xcls(int) { return 0; }
-  __device__ static constexpr int ycls(int) { return 0; }
-};
-template <>
-struct Layout<5> {
-  // c = (p, p, q, p, p): x classes {p, q}; y classes {(p + p)/2, (p + q)/2, half}
-  static constexpr int NX = 2, NY = 3;
-  __device__ static constexpr int xcls(int j) { return j == 2 ? 1 : 0; }
-  __device__ static constexpr int ycls(int j) { return (j == 1 || j == 2) ? 1 : 0; }
-};
-
-// Coefficient phases of the per-point rotations (host: coefficient_phases): the
-// FP32 forms cycle through kDitherFP32 values of each coefficient, step k using
-// value k mod kDitherFP32.
-template <typename R>
-constexpr int phases_of() {
-  return sizeof(R) == 4 ? kDitherFP32 : 1;
-}
-
-// Period of a solve's step pattern: the coefficient phases and, for alternating
-// shears, the orientation parity.  Steps run in groups that start at multiples of
-// it, so inside a group every step's pattern is a compile-time constant.
-template <typename R, int SH>
-constexpr int step_period() {
-  return (SH == kShearAlt && phases_of<R>() % 2 != 0) ? 2 * phases_of<R>() : phases_of<R>();
-}
 
 // The Bloch vectors of a lane's points and their per-point rotations.
 template <typename R, int PPL, int FORM, int NS, int POL, int SH>
@@ -421,7 +261,7 @@ __device__ __forceinline__ void steps_lds(BlochLanes<R, PPL, FORM, NS, POL, SH>&
   using Row = RowN<R, Lanes::kRow>;
   constexpr int P = Lanes::P;
   const Row* __restrict__ tab = reinterpret_cast<const Row*>(table);
-  extern __shared__ unsigned char pd_lds[];
+  extern __shared__ __align__(16) unsigned char pd_lds[];
   Row* rows = reinterpret_cast<Row*>(pd_lds);
   while (k < k_full) {
     long long cend = (k / chunk + 1) * chunk;
@@ -584,8 +424,8 @@ __global__ void __launch_bounds__(256) strang_kernel(const SolveParams p) {
 // in the single-solve kernel, so each solve's result does not depend on the
 // batch it runs in.
 
-__global__ void batch_reset(unsigned int* counter) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;
+__global__ void batch_reset(unsigned int* counters) {
+  if (blockIdx.x == 0 && threadIdx.x < kBatchKinds) counters[threadIdx.x] = 0u;
 }
 
 template <int PPL>
@@ -618,6 +458,37 @@ __global__ void __launch_bounds__(256) batch_kernel(const BatchSolve* __restrict
       else
         strang_tile<double, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
     }
+  }
+}
+
+// The same for solves by columns, in a kernel of its own: its 128 registers let four blocks
+// of 256 threads stay on a compute unit, where both kinds of tile in one kernel took 178 and
+// held two.  Sixteen FP32 solves of 128^2 to 1024^2 points: 5.9 ms by rows, 4.2 by columns.
+template <int PPL>
+__global__ void __launch_bounds__(256, 4) batch_columns_kernel(const BatchSolve* __restrict__ solves,
+                                                               const BatchItem* __restrict__ items, int n_items,
+                                                               unsigned int* counter) {
+  __shared__ int next;
+  extern __shared__ __align__(16) unsigned char pd_lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (;;) {
+    __syncthreads();  // every lane has read the previous item index
+    if (threadIdx.x == 0) next = (int)atomicAdd(counter, 1u);
+    __syncthreads();
+    // told uniform, so that the item, the solve's parameters and with them the loops'
+    // bounds stay in scalar registers
+    const int it = __builtin_amdgcn_readfirstlane(next);
+    if (it >= n_items) return;
+    const BatchItem w = items[it];
+    const BatchSolve s = solves[w.solve];
+    unsigned char* lds = pd_lds + wave * kColumnLdsWave;
+    const int unit = (int)w.base + wave;
+    if (s.precision == PD_FP32)
+      column_tile<float, PPL, 1, 0, kShearOnce>(s.p, unit, lds);
+    else if (s.precision == PD_FP32_FAST)
+      column_tile<float, PPL, 1, 0, kShearAlt>(s.p, unit, lds);
+    else
+      column_tile<double, PPL, 1, 0, kShearPlain>(s.p, unit, lds);
   }
 }
 
@@ -1093,12 +964,9 @@ __global__ void __launch_bounds__(kRedThreads) batch_density_finish(const Densit
   }
 }
 
-// A dispatch packet holds a grid's size in work-items in 32 bits, so one launch
-// covers at most kMaxLanes lanes; a larger grid (up to 65536 x 65536 points at one
-// point per lane) runs as consecutive launches over point ranges, each starting at
-// a multiple of the block's span, so every point sees the same tile as in one launch.
-constexpr long long kMaxLanes = 1LL << 31;
-
+// A larger grid than kMaxLanes points (up to 65536 x 65536 at one point per lane) runs as
+// consecutive launches over point ranges, each starting at a multiple of the block's span,
+// so every point sees the same tile as in one launch.
 // Launch `launch(q, blocks)` over the grid in slices of at most kMaxLanes lanes,
 // q.first being the slice's first point.
 template <typename F>
@@ -1193,6 +1061,11 @@ long long density_partials(long long npts) { return (npts + kRedTile - 1) / kRed
 hipError_t launch_propagate(int scheme, int precision, int ppl, int block, int taylor, int elliptic,
                             const SolveParams& p, hipStream_t stream) {
   const int S = (scheme == PD_SCHEME_STRANG4 || scheme == PD_SCHEME_MIDPOINT4) ? 5 : 1;
+  if (base_scheme(scheme) == PD_SCHEME_STRANG && p.series) {
+    if (precision == PD_FP32) return columns_variant<float, kShearOnce>(S, elliptic, ppl, block, p, stream);
+    if (precision == PD_FP32_FAST) return columns_variant<float, kShearAlt>(S, elliptic, ppl, block, p, stream);
+    return columns_variant<double, kShearPlain>(S, elliptic, ppl, block, p, stream);
+  }
   if (base_scheme(scheme) == PD_SCHEME_STRANG) {
     if (precision == PD_FP32)
       return p.form == kFormShear ? strang_variant<float, kFormShear, kShearOnce>(S, elliptic, ppl, block, p, stream)
@@ -1315,33 +1188,33 @@ hipError_t launch_batch_density(const DensityJob* jobs, int n_jobs, long long to
   return hipGetLastError();
 }
 
-hipError_t launch_batch(int ppl, int block, int grid_blocks, const BatchSolve* solves, const BatchItem* items,
-                        int n_items, unsigned int* counter, hipStream_t stream) {
-  hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, stream, counter);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  switch (ppl) {
-    case 1:
-      hipLaunchKernelGGL(batch_kernel<1>, dim3(grid_blocks), dim3(block), 0, stream, solves, items, n_items, counter);
-      break;
-    case 2:
-      hipLaunchKernelGGL(batch_kernel<2>, dim3(grid_blocks), dim3(block), 0, stream, solves, items, n_items, counter);
-      break;
-    default:
-      hipLaunchKernelGGL(batch_kernel<4>, dim3(grid_blocks), dim3(block), 0, stream, solves, items, n_items, counter);
-      break;
-  }
+namespace {
+size_t batch_lds(int kind, int block) { return kind == kBatchColumns ? (size_t)(block / 64) * kColumnLdsWave : 0; }
+
+using BatchKernel = void (*)(const BatchSolve*, const BatchItem*, int, unsigned int*);
+BatchKernel batch_kernel_of(int kind, int ppl) {
+  if (kind == kBatchColumns)
+    return ppl == 1 ? batch_columns_kernel<1> : ppl == 2 ? batch_columns_kernel<2> : batch_columns_kernel<4>;
+  return ppl == 1 ? batch_kernel<1> : ppl == 2 ? batch_kernel<2> : batch_kernel<4>;
+}
+}  // namespace
+
+hipError_t launch_batch_reset(unsigned int* counters, hipStream_t stream) {
+  hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, stream, counters);
   return hipGetLastError();
 }
 
-int batch_blocks_per_cu(int ppl, int block) {
+hipError_t launch_batch(int kind, int ppl, int block, int grid_blocks, const BatchSolve* solves,
+                        const BatchItem* items, int n_items, unsigned int* counter, hipStream_t stream) {
+  hipLaunchKernelGGL(batch_kernel_of(kind, ppl), dim3(grid_blocks), dim3(block), batch_lds(kind, block), stream, solves,
+                     items, n_items, counter);
+  return hipGetLastError();
+}
+
+int batch_blocks_per_cu(int kind, int ppl, int block) {
   int n = 0;
-  hipError_t e;
-  switch (ppl) {
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<1>, block, 0); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<2>, block, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_kernel<4>, block, 0); break;
-  }
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &n, reinterpret_cast<const void*>(batch_kernel_of(kind, ppl)), block, batch_lds(kind, block));
   return (e == hipSuccess && n > 0) ? n : 1;
 }
 

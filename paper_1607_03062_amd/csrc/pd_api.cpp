@@ -138,6 +138,7 @@ SolveParams pd_grid_s::solve_params(long long k_begin, long long k_end, void* st
   SolveParams p{};
   p.npts = grid.points();
   p.nx = grid.nx;
+  p.ny = grid.ny;
   p.px_min = grid.px_min;
   p.dx = grid.dx;
   p.py_min = grid.py_min;
@@ -148,7 +149,7 @@ SolveParams pd_grid_s::solve_params(long long k_begin, long long k_end, void* st
   p.Ay_in = field.Ay_in;
   p.Ay_out = field.Ay_out;
   p.vsign = vsign();
-  // midpoint: per-point phase multipliers vsign c dt of the distinct stage coefficients
+  // half-angle multipliers vsign c dt of the distinct stage coefficients
   p.hx[0] = vsign() * (field.comp.c[0] * field.dt);
   p.hx[1] = vsign() * (field.comp.c[2] * field.dt);
   p.n_steps = field.n_steps;
@@ -166,6 +167,8 @@ SolveParams pd_grid_s::solve_params(long long k_begin, long long k_end, void* st
   p.stage = (table_stage == 1 && (size_t)chunk_steps * row_bytes <= 65536) ? 1 : 0;
   p.chunk_steps = chunk_steps;
   p.form = form;
+  p.series = series;
+  if (series) p.columns = columns(shape_points(), true);
   return p;
 }
 
@@ -230,6 +233,20 @@ pd_status prepare_field(pd_grid g, const pd_field* f, long long n_steps, FieldTa
   return ok();
 }
 
+// Bytes of the tables of a solve without a y component (the row kernel's, where the
+// scheme is Strang: step rows, column and row coefficients).
+size_t table_footprint(pd_grid g, long long n_steps) {
+  auto align = [](size_t n) { return (n + 255) / 256 * 256; };
+  size_t table = (size_t)table_rows(g->scheme, 0, n_steps) * table_row_bytes(g->scheme, g->precision, 0);
+  if (base_scheme(g->scheme) == PD_SCHEME_STRANG) {
+    const size_t v = is_fp32(g->precision) ? sizeof(float) : sizeof(double);
+    size_t col = align(table);
+    size_t row = align(col + 2 * point_coefficient_pairs_x(g->scheme, g->precision) * v * (size_t)g->grid.nx);
+    table = align(row + 2 * point_coefficient_pairs_y(g->scheme, g->precision) * v * (size_t)g->grid.ny);
+  }
+  return table;
+}
+
 void fill_info(pd_grid g, const FieldTables& t, long long masked, long long steps_done, pd_info* out) {
   std::memset(out, 0, sizeof *out);
   out->n_points = g->grid.points();
@@ -246,7 +263,7 @@ void fill_info(pd_grid g, const FieldTables& t, long long masked, long long step
   out->A_max = t.A_max;
   out->precision = g->precision;
   out->scheme = g->scheme;
-  out->points_per_lane = g->points_per_lane;
+  out->points_per_lane = g->shape_points();
   out->block_threads = g->block_threads;
   out->table_stage = g->table_stage;
   out->chunk_steps = g->chunk_steps;
@@ -388,11 +405,14 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   int taylor = 0, form = 0;
   pd_status s = prepare_field(g, f, n_steps, &t, &masked, &taylor, &form);
   if (s != PD_OK) return s;
+  const bool strang = base_scheme(g->scheme) == PD_SCHEME_STRANG;
+  const int series = strang ? column_series(g->grid, t, g->precision) : 0;
   std::vector<unsigned char> rows;
-  build_step_table(t, g->scheme, g->precision, form, g->vsign(), &rows);
+  build_step_table(t, g->scheme, g->precision, form, series != 0, g->vsign(), &rows);
   size_t col_offset = 0, row_offset = 0;
-  if (base_scheme(g->scheme) == PD_SCHEME_STRANG)
-    build_point_coefficients(g->grid, t, g->scheme, g->precision, form, g->vsign(), &rows, &col_offset, &row_offset);
+  if (strang)
+    build_point_coefficients(g->grid, t, g->scheme, g->precision, form, series != 0, g->vsign(), &rows, &col_offset,
+                             &row_offset);
 
   if (g->device < 0) {
     int dev = -1;
@@ -406,12 +426,15 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   // Work of an earlier solve on this handle may still read the table or the state.
   if ((s = wait_own_work(g)) != PD_OK) return s;
   g->field_set = false;
-  if (rows.size() > g->table_capacity) {
+  // the footprint pd_solve_bytes states, which no field enters: at least what the row
+  // kernel's tables take
+  const size_t table_need = std::max(rows.size(), table_footprint(g, n_steps));
+  if (table_need > g->table_capacity) {
     release(g->d_table);
     g->table_bytes = g->table_capacity = 0;
-    e = device_malloc(&g->d_table, rows.size());
+    e = device_malloc(&g->d_table, table_need);
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(field table)");
-    g->table_capacity = rows.size();
+    g->table_capacity = table_need;
   }
   g->table_bytes = rows.size();
   e = hipMemcpy(g->d_table, rows.data(), rows.size(), hipMemcpyHostToDevice);
@@ -431,6 +454,7 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   g->n_masked = masked;
   g->taylor = taylor;
   g->form = form;
+  g->series = series;
   g->col_offset = col_offset;
   g->row_offset = row_offset;
   g->steps_done = 0;
@@ -443,17 +467,9 @@ size_t pd_state_bytes(pd_grid g) { return g ? g->state_bytes() : 0; }
 
 size_t pd_solve_bytes(pd_grid g, long long n_steps) {
   if (!g || n_steps < 1) return 0;
-  auto align = [](size_t n) { return (n + 255) / 256 * 256; };
-  size_t table = (size_t)table_rows(g->scheme, 0, n_steps) * table_row_bytes(g->scheme, g->precision, 0);
-  if (base_scheme(g->scheme) == PD_SCHEME_STRANG) {
-    const size_t v = is_fp32(g->precision) ? sizeof(float) : sizeof(double);
-    size_t col = align(table);
-    size_t row = align(col + 2 * point_coefficient_pairs_x(g->scheme, g->precision) * v * (size_t)g->grid.nx);
-    table = align(row + 2 * point_coefficient_pairs_y(g->scheme, g->precision) * v * (size_t)g->grid.ny);
-  }
   const size_t npts = (size_t)g->grid.points();
-  return table + npts * sizeof(double) + (size_t)density_partials((long long)npts) * sizeof(double) +
-         sizeof(double) + g->state_bytes();
+  return table_footprint(g, n_steps) + npts * sizeof(double) +
+         (size_t)density_partials((long long)npts) * sizeof(double) + sizeof(double) + g->state_bytes();
 }
 
 pd_status pd_bind_state(pd_grid g, void* dev_ptr, size_t bytes) {
@@ -541,7 +557,10 @@ pd_status pd_set_launch(pd_grid g, int points_per_lane, int block_threads, int t
     if (chunk_steps < 64 || chunk_steps > max_chunk || (chunk_steps & (chunk_steps - 1)) != 0)
       return fail(PD_ERR_INVALID, "chunk_steps must be a power of two in [64, %d]", max_chunk);
   }
-  if (points_per_lane) g->points_per_lane = points_per_lane;
+  if (points_per_lane) {
+    g->points_per_lane = points_per_lane;
+    g->points_chosen = true;
+  }
   if (block_threads) g->block_threads = block_threads;
   if (table_stage) g->table_stage = table_stage;
   if (chunk_steps) g->chunk_steps = chunk_steps;
@@ -576,7 +595,7 @@ pd_status pd_propagate(pd_grid g, long long max_steps, void* stream) {
   }
   const SolveParams p = g->solve_params(k_begin, k_end, st);
   if (fault_now(kFaultLaunch)) return fail(PD_ERR_DEVICE, "injected launch fault (PD_FAULT)");
-  hipError_t e = launch_propagate(g->scheme, g->precision, g->points_per_lane, g->block_threads, g->taylor,
+  hipError_t e = launch_propagate(g->scheme, g->precision, g->shape_points(), g->block_threads, g->taylor,
                                   g->field.elliptic ? 1 : 0, p, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "propagate launch");
   g->steps_done = p.k_end;

@@ -101,7 +101,10 @@ void boundary_A(const FieldTables& t, long long k, double* ax, double* ay);
 size_t table_row_values(int scheme, int elliptic);
 size_t table_row_bytes(int scheme, int precision, int elliptic);
 long long table_rows(int scheme, int elliptic, long long n_steps);
-void build_step_table(const FieldTables& t, int scheme, int precision, int form, double vsign,
+//   Strang by columns (`columns`): as for midpoint, FP64 in every precision; with a y
+//           component the half angles of the field part of the y rotation after each
+//           stage, and one more row with (in its first y slot) the opening half step's.
+void build_step_table(const FieldTables& t, int scheme, int precision, int form, bool columns, double vsign,
                       std::vector<unsigned char>* rows);
 // Rotation form of a Strang solve: shears when every rotation angle is small enough.
 int strang_form(const Grid& g, const FieldTables& t);
@@ -124,9 +127,11 @@ inline int coefficient_phases(int precision) { return is_fp32(precision) ? kDith
 // half step (1 pair), in the solve's form and precision, appended to `bytes`
 // (each block 256-byte aligned).  Every pair except the half step is stored once
 // per coefficient phase, phase-minor: pair q of phase h at index q * phases + h.
-// Returns the byte offsets of the two blocks.
-void build_point_coefficients(const Grid& g, const FieldTables& t, int scheme, int precision, int form, double vsign,
-                              std::vector<unsigned char>* bytes, size_t* col_offset, size_t* row_offset);
+// Returns the byte offsets of the two blocks.  `columns` (the solve runs by columns): no
+// column block, which the column kernels do not read.
+void build_point_coefficients(const Grid& g, const FieldTables& t, int scheme, int precision, int form, bool columns,
+                              double vsign, std::vector<unsigned char>* bytes, size_t* col_offset,
+                              size_t* row_offset);
 size_t point_coefficient_pairs_x(int scheme, int precision);  // per column, phases included
 size_t point_coefficient_pairs_y(int scheme, int precision);  // per row, phases and the half step included
 // Coefficients (a, s) of the rotation by phi = 2 * half in a rotation form.
@@ -152,7 +157,7 @@ constexpr long long kRenormEvery = 1024;
 // Coefficients of tan(sqrt x) / sqrt x = sum_{n >= 1} a_n x^(n-1).  From
 // tan' = 1 + tan^2: a_1 = 1 and (2n - 1) a_n = sum_{k=1}^{n-1} a_k a_{n-k}.
 constexpr double tan_series_coef(int n) {
-  double a[24] = {};
+  double a[32] = {};
   a[1] = 1.0;
   for (int m = 2; m <= n; ++m) {
     double s = 0.0;
@@ -161,6 +166,46 @@ constexpr double tan_series_coef(int n) {
   }
   return a[n];
 }
+
+// Coefficients of sin(2 sqrt x) / (2 sqrt x) = sum_{n >= 1} b_n x^(n-1), b_n = (-4)^(n-1) / (2n-1)!.
+constexpr double sin2_series_coef(int n) {
+  double b = 1.0;
+  for (int m = 2; m <= n; ++m) b *= -4.0 / ((2 * m - 2) * (2 * m - 1));
+  return b;
+}
+
+// Strang solves by columns (strang_columns.h): the two rotations about x of a stage run as
+// one, whose coefficients a wave evaluates for its columns.
+//
+// Terms of the series a solve's coefficients take (3, 5, or 8 to kSeriesMax in fours), or 0 where
+// the solve runs the row kernel: a rotation form other than shears, a half angle of more
+// than pi/4, or fewer than kColumnMinRows rows.  The choice rests on the grid, the field
+// and the precision alone, never on the launch shape, so that every way to run a solve
+// gives the same bits.
+constexpr int kSeriesMax = 28;
+constexpr int kColumnMinRows = 32;
+int column_series(const Grid& g, const FieldTables& t, int precision);
+
+// How a grid's points are dealt to the waves of a column kernel: a wave takes 2^cshift
+// neighbouring columns and 64 / 2^cshift bands of points_per_lane rows of them (segs such
+// pieces cover a column), and evaluates coefficients for `chunk` steps at a time.  Units
+// (waves) go through 16 columns at a time: the columns of a 128-byte line of n(p).
+struct ColumnGeometry {
+  int cshift, segs, units, chunk;
+};
+constexpr int kColumnSuperShift = 4;
+constexpr int kColumnEntries = 512;     // coefficient pairs of a column and chunk, at most
+constexpr int kColumnPairBytes = 8192;  // LDS bytes for a wave's pairs
+// 16 bytes after each column's pairs, room for reads 16 steps past the end, and a slot for
+// lanes without an entry
+constexpr int kColumnLdsWave = kColumnPairBytes + 17 * 16 + 256 + 16;
+// Points per lane of a column solve whose caller set none: 1, 2, 4 or 8.
+int column_points_per_lane(const Grid& g, int precision, int elliptic);
+ColumnGeometry column_geometry(const Grid& g, int precision, int stages, int elliptic, int points_per_lane, bool alone);
+
+// A dispatch packet holds a grid's size in work-items in 32 bits, so one launch covers at
+// most this many lanes; a larger grid runs as consecutive launches.
+constexpr long long kMaxLanes = 1LL << 31;
 
 // Midpoint form of a solve: tangent when the state's growth over kRenormEvery
 // steps stays below 2^32 and a compiled series order reaches the precision's
@@ -180,12 +225,12 @@ struct SolveParams {
   long long first;   // first point (Strang) or lane (midpoint: lanes cover bands of rows column
                      // by column) of this launch: a grid of more than 2^31 lanes runs as
                      // several launches over consecutive ranges
-  int nx;
+  int nx, ny;
   double px_min, dx, py_min, dy;
   double A_in, A_out, dt;
   double Ay_in, Ay_out;
   double vsign;      // +1: valley K+, -1: K- (H = -sigma.P)
-  double hx[2];      // midpoint: vsign * c dt for the distinct stage coefficients
+  double hx[2];      // vsign * c dt for the distinct stage coefficients
   long long n_steps, k_begin, k_end;
   const void* table;
   const void* col_coef;  // Strang: per column the (a, s) pairs of the x rotations by 2 c dt px
@@ -197,6 +242,8 @@ struct SolveParams {
   int stage;         // Strang table path: 0 scalar-unit loads, 1 LDS chunks
   int form;          // Strang: kFormShear or kFormVersine; midpoint: kMidTangent or kMidCosine
   long long chunk_steps;  // LDS chunk length in steps (power of two; divides 1024 in FP32)
+  int series;             // Strang by columns: terms of the coefficients' series (0: the row kernel)
+  ColumnGeometry columns;
 };
 
 // Projection of a stored state at step k on the positive-energy state of
@@ -215,7 +262,8 @@ struct BatchSolve {
 };
 
 // One work item of a batched launch: the tile of block_threads * points_per_lane
-// points of solve `solve` starting at point `base`.
+// points of solve `solve` starting at point `base`, or (by columns) the block's waves'
+// units of it from unit `base`.
 struct BatchItem {
   int solve;
   int pad;
@@ -248,10 +296,14 @@ constexpr long long kStaticPartials = kStaticMaxPoints / 2048;
 // Device address of the static scratch on `device` (kStaticPartials partials, then
 // one sum), looked up on the first call for that device.
 hipError_t static_scratch(int device, double** out);
-hipError_t launch_batch(int points_per_lane, int block_threads, int grid_blocks, const BatchSolve* solves,
+// The persistent kernels of a batch: tiles of the row kernel, and waves' units of the
+// column kernels.  Each has its own work items and its own counter.
+constexpr int kBatchRows = 0, kBatchColumns = 1, kBatchKinds = 2;
+hipError_t launch_batch_reset(unsigned int* counters, hipStream_t stream);
+hipError_t launch_batch(int kind, int points_per_lane, int block_threads, int grid_blocks, const BatchSolve* solves,
                         const BatchItem* items, int n_items, unsigned int* counter, hipStream_t stream);
 hipError_t launch_batch_density(const DensityJob* jobs, int n_jobs, long long total_tiles, hipStream_t stream);
-int batch_blocks_per_cu(int points_per_lane, int block_threads);
+int batch_blocks_per_cu(int kind, int points_per_lane, int block_threads);
 long long density_partials(long long npts);
 size_t state_values_per_point(int scheme);
 
@@ -263,6 +315,7 @@ struct pd_grid_s {
   int precision = PD_FP64;
   int scheme = PD_SCHEME_STRANG;
   int points_per_lane = 2;
+  bool points_chosen = false;  // points_per_lane set by the caller or the autotuner
   int block_threads = 256;
   int table_stage = 2;  // 1: LDS chunks, 2: scalar-unit reads
   int chunk_steps = 512;
@@ -274,6 +327,7 @@ struct pd_grid_s {
   long long steps_done = 0;
   int taylor = 0;
   int form = pdx::kFormShear;  // Strang rotation form of the current field
+  int series = 0;              // Strang by columns: terms of the coefficients' series, 0: the row kernel
   int valley = PD_VALLEYS_BOTH;
   double vsign() const { return valley == PD_VALLEY_KMINUS ? -1.0 : 1.0; }
 
@@ -309,6 +363,21 @@ struct pd_grid_s {
   double density_scale() const;
   // Launch parameters of steps [k_begin, k_end); `state` is the chunk state buffer (may be null).
   pdx::SolveParams solve_params(long long k_begin, long long k_end, void* state) const;
+  // Points per lane the solve runs with.
+  int shape_points() const {
+    if (points_chosen || !field_set || !series) return points_per_lane;
+    return pdx::column_points_per_lane(grid, precision, field.elliptic ? 1 : 0);
+  }
+  // alone: the solve's own launch; else a member of a batch's persistent launch
+  pdx::ColumnGeometry columns(int ppl, bool alone) const {
+    return pdx::column_geometry(grid, precision, field.comp.stages, field.elliptic ? 1 : 0, ppl, alone);
+  }
+  // Work items of the persistent batch kernel and the step from one's base to the next's
+  long long batch_tiles(int ppl, int block, long long* span) const {
+    const long long total = series ? columns(ppl, false).units : grid.points();
+    *span = series ? block / 64 : (long long)block * ppl;
+    return (total + *span - 1) / *span;
+  }
 };
 
 namespace pdx {
