@@ -537,17 +537,6 @@ int column_series(const Grid& g, const FieldTables& t, int precision) {
   return kSeriesMax;
 }
 
-int column_points_per_lane(const Grid& g, int precision, int elliptic) {
-  // More points per lane: fewer LDS reads and coefficients for a point's step, as long as
-  // every SIMD keeps a wave (FP64, whose FMAs a wave with a few points issues without gaps),
-  // or two (FP32: two waves' FMAs issue together).  The device has 1024 SIMDs.
-  const long long waves = is_fp32(precision) ? 2048 : 1024;
-  // eight points with a y component in FP32 take more than half of the registers
-  for (int ppl = is_fp32(precision) && elliptic ? 4 : 8; ppl > 1; ppl /= 2)
-    if (g.points() >= 64 * ppl * waves) return ppl;
-  return 1;
-}
-
 ColumnGeometry column_geometry(const Grid& g, int precision, int stages, int elliptic, int points_per_lane,
                                bool alone) {
   const int pair = is_fp32(precision) ? 8 : 16;
@@ -575,6 +564,53 @@ ColumnGeometry column_geometry(const Grid& g, int precision, int stages, int ell
       best_cost = cost;
     }
     if (s == 0 && alone && waves <= 1024.0) break;
+  }
+  return best;
+}
+
+namespace {
+
+// Time of a launch of `waves` waves of `ppl` points a lane, in issue slots of a point's step:
+// the waves of the fullest of the device's 1024 SIMDs, one after another, a point's share of
+// what its lane's points have in common (`shared`, of one point's step) on top.  FP32
+// instructions of two waves issue together, so that a wave without a partner takes more than
+// its turn; at 8 points a SIMD holds two waves (FP32) at a time.
+double shape_cost(long long waves, int ppl, bool fp32, double shared) {
+  long long n = (waves + 1023) / 1024;
+  if (fp32 && ppl == 8) n += n % 2;
+  const double turns = n == 1 ? (fp32 ? 1.8 : 1.12) : n + (fp32 && n % 2 ? 0.4 : 0.0);
+  return turns * ppl * (1.0 + shared / ppl);
+}
+
+}  // namespace
+
+int auto_points_per_lane(const Grid& g, int scheme, int precision, int stages, int elliptic) {
+  const bool mid = base_scheme(scheme) == PD_SCHEME_MIDPOINT, f32 = is_fp32(precision);
+  // midpoint: the column's phase (1 of 16 instructions; with its conversion, unpaired, 4 of
+  // 36 FP32 slots), up to 4 points.  Columns: the coefficients' evaluation and reads, up to 8
+  // points; with a y component in FP32 8 would take more than half of the registers.
+  // Measured, 20000 steps, 1 / 2 / 4 / 8 points: columns FP32 256^2 0.38 / 0.64 / - / - ms,
+  // 512^2 0.85 / 0.82 / 1.11 / -, 1024^2 - / 2.99 / 2.98 / 2.80; FP64 256^2 0.44 / 0.65 / - / -,
+  // 512^2 1.26 / 1.18 / 1.14 / 1.88, 1024^2 - / 4.44 / 4.23 / 4.15; midpoint FP64 64^2 x 4000
+  // 0.15 / 0.27 / 0.51, 700 x 511 x 8000 1.71 / 1.65 / 2.05, FP32 256^2 x 4000 0.21 / 0.31 /
+  // 0.55, 1024^2 x 10000 3.24 / 3.08 / 3.00.
+  const double shared = mid ? (f32 ? 0.11 : 0.065) : (f32 ? 0.22 : 0.16);
+  const int most = mid || (f32 && elliptic) ? 4 : 8;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int ppl = 1; ppl <= most; ppl *= 2) {
+    long long waves;
+    if (mid) {
+      waves = ((g.ny + ppl - 1) / ppl * (long long)g.nx + 63) / 64;
+    } else {
+      const ColumnGeometry c = column_geometry(g, precision, stages, elliptic, ppl, true);
+      waves = c.segs * (((long long)g.nx + (1 << c.cshift) - 1) >> c.cshift);
+    }
+    const double cost = shape_cost(waves, ppl, f32, shared);
+    if (ppl == 1 || cost < best_cost) {
+      best = ppl;
+      best_cost = cost;
+    }
   }
   return best;
 }

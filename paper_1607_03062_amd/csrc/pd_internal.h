@@ -199,8 +199,8 @@ constexpr int kColumnPairBytes = 8192;  // LDS bytes for a wave's pairs
 // 16 bytes after each column's pairs, room for reads 16 steps past the end, and a slot for
 // lanes without an entry
 constexpr int kColumnLdsWave = kColumnPairBytes + 17 * 16 + 256 + 16;
-// Points per lane of a column solve whose caller set none: 1, 2, 4 or 8.
-int column_points_per_lane(const Grid& g, int precision, int elliptic);
+// Points per lane of a column or midpoint solve whose caller set none: 1, 2, 4 or (columns) 8.
+int auto_points_per_lane(const Grid& g, int scheme, int precision, int stages, int elliptic);
 ColumnGeometry column_geometry(const Grid& g, int precision, int stages, int elliptic, int points_per_lane, bool alone);
 
 // A dispatch packet holds a grid's size in work-items in 32 bits, so one launch covers at
@@ -365,8 +365,9 @@ struct pd_grid_s {
   pdx::SolveParams solve_params(long long k_begin, long long k_end, void* state) const;
   // Points per lane the solve runs with.
   int shape_points() const {
-    if (points_chosen || !field_set || !series) return points_per_lane;
-    return pdx::column_points_per_lane(grid, precision, field.elliptic ? 1 : 0);
+    if (points_chosen || !field_set) return points_per_lane;
+    if (!series && pdx::base_scheme(scheme) != PD_SCHEME_MIDPOINT) return points_per_lane;
+    return pdx::auto_points_per_lane(grid, scheme, precision, field.comp.stages, field.elliptic ? 1 : 0);
   }
   // alone: the solve's own launch; else a member of a batch's persistent launch
   pdx::ColumnGeometry columns(int ppl, bool alone) const {

@@ -36,9 +36,10 @@ def test_edges_of_the_tiling(gpu, nx, ny, precision):
         assert np.array_equal(n, ref[0]) and rho == ref[1], (ppl, block)
 
 
-# eight points per lane is what large grids take: 2^19 points (FP64), 2^20 (FP32)
-@pytest.mark.parametrize("precision,nx,ny", [("fp64", 1030, 517), ("fp32", 1030, 1021), ("fp32fast", 1030, 1021)])
-def test_eight_points_per_lane(gpu, precision, nx, ny):
+# eight points per lane, which large grids take where they fill the device evenly
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32fast"])
+def test_eight_points_per_lane(gpu, precision):
+    nx, ny = 1019, 1021
     g, f, N = _grid(nx, ny), wl.sin2(0.3, 0.6, 3), 700
     ref = run(gpu, g, f, N, precision)
     assert ref[2]["points_per_lane"] == 8
