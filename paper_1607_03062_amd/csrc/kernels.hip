@@ -808,81 +808,86 @@ __global__ void __launch_bounds__(256) midpoint_kernel(const SolveParams p) {
 
 // ---------------------------------------------------------------------------
 // Snapshots: the state after k steps (in the state buffer, or v_in at k = 0)
-// projected on the positive-energy state of sigma.(p + A(t_k)).
+// projected on the positive-energy state of sigma.(p + A(t_k)); a point's value as a
+// source of the density pass below.
 
 template <typename R, int POL>
-__global__ void __launch_bounds__(256) strang_snapshot_kernel(const SolveParams p, const SnapshotParams s,
-                                                              int half_offset, int row_stride) {
-  const long long idx = p.first + (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= p.npts) return;
-  PointCoords c = coords(p, idx);
-  double Pxi = c.px + p.A_in, Pyi = c.py + p.Ay_in;
-  double Px = c.px + s.Ax, Py = c.py + s.Ay;
-  double Ei = sqrt(Pxi * Pxi + Pyi * Pyi), E = sqrt(Px * Px + Py * Py);
-  double n = 0.0;
-  if (Ei > 0.0 && E > 0.0) {
-    double X, Y, Z;
-    if (p.load_state) {
-      const R* st = static_cast<const R*>(p.state);
-      R x = st[idx], y = st[p.npts + idx], z = st[2 * p.npts + idx];
-      // the stored state is ahead by the opening half step of step k: undo it
-      // (field part first, then the per-point part, each by its inverse rotation)
-      const R* rowc = static_cast<const R*>(p.row_coef);
-      R ha = rowc[(size_t)row_stride * c.j + half_offset], hs = rowc[(size_t)row_stride * c.j + half_offset + 1];
-      if (POL) {
+struct StrangSnapshot {
+  SolveParams p;
+  SnapshotParams s;
+  int half_offset, row_stride;
+  __device__ __forceinline__ double operator()(long long idx) const {
+    PointCoords c = coords(p, idx);
+    double Pxi = c.px + p.A_in, Pyi = c.py + p.Ay_in;
+    double Px = c.px + s.Ax, Py = c.py + s.Ay;
+    double Ei = sqrt(Pxi * Pxi + Pyi * Pyi), E = sqrt(Px * Px + Py * Py);
+    double n = 0.0;
+    if (Ei > 0.0 && E > 0.0) {
+      double X, Y, Z;
+      if (p.load_state) {
+        const R* st = static_cast<const R*>(p.state);
+        R x = st[idx], y = st[p.npts + idx], z = st[2 * p.npts + idx];
+        // the stored state is ahead by the opening half step of step k: undo it
+        // (field part first, then the per-point part, each by its inverse rotation)
+        const R* rowc = static_cast<const R*>(p.row_coef);
+        R ha = rowc[(size_t)row_stride * c.j + half_offset], hs = rowc[(size_t)row_stride * c.j + half_offset + 1];
+        if (POL) {
+          if (p.form == kFormShear)
+            rotate_shear(z, x, (R)s.undo_a, (R)s.undo_s);
+          else
+            rotate_versine(z, x, (R)s.undo_a, (R)s.undo_s);
+        }
         if (p.form == kFormShear)
-          rotate_shear(z, x, (R)s.undo_a, (R)s.undo_s);
+          rotate_shear(z, x, -ha, -hs);
         else
-          rotate_versine(z, x, (R)s.undo_a, (R)s.undo_s);
+          rotate_versine(z, x, ha, -hs);
+        X = x;
+        Y = y;
+        Z = z;
+      } else {
+        X = -p.vsign * Pxi / Ei;
+        Y = -p.vsign * Pyi / Ei;
+        Z = 0.0;
       }
-      if (p.form == kFormShear)
-        rotate_shear(z, x, -ha, -hs);
-      else
-        rotate_versine(z, x, ha, -hs);
-      X = x;
-      Y = y;
-      Z = z;
-    } else {
-      X = -p.vsign * Pxi / Ei;
-      Y = -p.vsign * Pyi / Ei;
-      Z = 0.0;
-    }
-    double nr = sqrt(X * X + Y * Y + Z * Z);
-    if (nr > 0.0) n = (E + p.vsign * (Px * X + Py * Y) / nr) / (2.0 * E);
+      double nr = sqrt(X * X + Y * Y + Z * Z);
+      if (nr > 0.0) n = (E + p.vsign * (Px * X + Py * Y) / nr) / (2.0 * E);
   }
-  p.n_out[idx] = n;
-}
+  return n;
+  }
+};
 
 template <typename R>
-__global__ void __launch_bounds__(256) midpoint_snapshot_kernel(const SolveParams p, const SnapshotParams s) {
-  const long long idx = p.first + (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= p.npts) return;
-  PointCoords c = coords(p, idx);
-  double Pxi = p.vsign * (c.px + p.A_in), Pyi = p.vsign * (c.py + p.Ay_in);
-  double Px = p.vsign * (c.px + s.Ax), Py = p.vsign * (c.py + s.Ay);
-  double Ei = sqrt(Pxi * Pxi + Pyi * Pyi), E = sqrt(Px * Px + Py * Py);
-  double n = 0.0;
-  if (Ei > 0.0 && E > 0.0) {
-    double A1, B1, A2, B2;
-    if (p.load_state) {
-      const R* st = static_cast<const R*>(p.state);
-      A1 = st[idx];
-      B1 = st[p.npts + idx];
-      A2 = st[2 * p.npts + idx];
-      B2 = st[3 * p.npts + idx];
-    } else {
-      double d = 1.4142135623730951 * Ei;
-      A1 = -Pxi / d;
-      B1 = Pyi / d;
-      A2 = Ei / d;
-      B2 = 0.0;
-    }
-    double re = (E * A1 + Px * A2) + Py * B2;
-    double im = (E * B1 + Px * B2) - Py * A2;
-    n = (re * re + im * im) / (2.0 * E * E) / (A1 * A1 + B1 * B1 + A2 * A2 + B2 * B2);
+struct MidpointSnapshot {
+  SolveParams p;
+  SnapshotParams s;
+  __device__ __forceinline__ double operator()(long long idx) const {
+    PointCoords c = coords(p, idx);
+    double Pxi = p.vsign * (c.px + p.A_in), Pyi = p.vsign * (c.py + p.Ay_in);
+    double Px = p.vsign * (c.px + s.Ax), Py = p.vsign * (c.py + s.Ay);
+    double Ei = sqrt(Pxi * Pxi + Pyi * Pyi), E = sqrt(Px * Px + Py * Py);
+    double n = 0.0;
+    if (Ei > 0.0 && E > 0.0) {
+      double A1, B1, A2, B2;
+      if (p.load_state) {
+        const R* st = static_cast<const R*>(p.state);
+        A1 = st[idx];
+        B1 = st[p.npts + idx];
+        A2 = st[2 * p.npts + idx];
+        B2 = st[3 * p.npts + idx];
+      } else {
+        double d = 1.4142135623730951 * Ei;
+        A1 = -Pxi / d;
+        B1 = Pyi / d;
+        A2 = Ei / d;
+        B2 = 0.0;
+      }
+      double re = (E * A1 + Px * A2) + Py * B2;
+      double im = (E * B1 + Px * B2) - Py * A2;
+      n = (re * re + im * im) / (2.0 * E * E) / (A1 * A1 + B1 * B1 + A2 * A2 + B2 * B2);
   }
-  p.n_out[idx] = n;
-}
+  return n;
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Density: rho = scale * sum n, in a fixed order that depends only on npts.
@@ -925,16 +930,68 @@ __device__ __forceinline__ double partials_sum(const double* __restrict__ partia
   return block_sum(s);
 }
 
-__global__ void __launch_bounds__(kRedThreads) density_tiles(const double* __restrict__ n, long long npts,
-                                                             double* __restrict__ partial) {
-  double s = tile_sum(n, npts, blockIdx.x);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
+// A stored n(p).
+struct StoredDensity {
+  const double* __restrict__ n;
+  __device__ __forceinline__ double operator()(long long i) const { return n[i]; }
+};
+
+// One pass over the points: a point's value from `value`, kept in n_store and copied to
+// n_copy (each may be null), its tile's sum into partial[tile].  `done` (null: a second
+// launch sums the partials): the blocks count themselves there, and the last one sums the
+// partials, writes rho and clears the count for the next pass.
+//
+// What bounds it: for small grids its own launch and the wait for it, so one launch does
+// what took four (values, tile sums, their sum, the copy of n) and the copy of rho to the
+// host; for large ones the memory, each value read and copied once.
+template <typename Value>
+__global__ void __launch_bounds__(kRedThreads) density_pass(const Value value, long long npts, double* n_store,
+                                                            double* n_copy, double* partial, unsigned* done,
+                                                            double scale, double* rho, double* rho_host) {
+  const long long tile = blockIdx.x, base = tile * kRedTile + threadIdx.x;
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < kRedPerThread; ++q) {
+    const long long i = base + (long long)q * kRedThreads;
+    if (i < npts) {
+      const double v = value(i);
+      s += v;
+      if (n_store) n_store[i] = v;
+      if (n_copy) n_copy[i] = v;
+    }
+  }
+  s = block_sum(s);
+  if (!done) {
+    if (threadIdx.x == 0) partial[tile] = s;
+    return;
+  }
+  __shared__ bool last;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(partial + tile, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x;
+  }
+  __syncthreads();
+  if (!last) return;
+  double r = 0.0;
+  for (unsigned i = threadIdx.x; i < gridDim.x; i += kRedThreads)
+    r += __hip_atomic_load(partial + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();  // the first sum's shared values have been read
+  r = block_sum(r);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *rho = scale * r;
+    if (rho_host) *rho_host = scale * r;
+  }
 }
 
 __global__ void __launch_bounds__(kRedThreads) density_finish(const double* __restrict__ partial, long long count,
-                                                              double scale, double* __restrict__ rho) {
+                                                              double scale, double* __restrict__ rho,
+                                                              double* __restrict__ rho_host) {
   double s = partials_sum(partial, count);
-  if (threadIdx.x == 0) *rho = scale * s;
+  if (threadIdx.x == 0) {
+    *rho = scale * s;
+    if (rho_host) *rho_host = scale * s;
+  }
 }
 
 // Batched densities: the tiles of every job in one launch (block -> job by
@@ -1105,43 +1162,50 @@ hipError_t launch_propagate(int scheme, int precision, int ppl, int block, int t
   }
 }
 
+namespace {
+
+// Tiles up to which the pass's last block sums the partials: beyond, the blocks' counting
+// costs more than the launch it saves.
+constexpr long long kOnePassTiles = 256;
+
+template <typename Value>
+hipError_t launch_pass(const Value& value, long long npts, double* n_store, const DensityOut& o, hipStream_t stream) {
+  const long long tiles = density_partials(npts);
+  unsigned* done = tiles <= kOnePassTiles ? o.done : nullptr;
+  hipLaunchKernelGGL((density_pass<Value>), dim3((unsigned)tiles), dim3(kRedThreads), 0, stream, value, npts, n_store,
+                     o.n_copy, o.partial, done, o.scale, o.rho, o.rho_host);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || done) return e;
+  hipLaunchKernelGGL(density_finish, dim3(1), dim3(kRedThreads), 0, stream, o.partial, tiles, o.scale, o.rho,
+                     o.rho_host);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_snapshot(int scheme, int precision, int elliptic, const SolveParams& p, const SnapshotParams& q,
-                           hipStream_t stream) {
-  return sliced_launch(p, 256, 1, [&](const SolveParams& ps, unsigned nb) {
-    if (base_scheme(scheme) == PD_SCHEME_STRANG) {
-      // per row: (stage classes) x (coefficient phases) pairs, then the half-step pair
-      const int classes = scheme == PD_SCHEME_STRANG4 ? 2 : 1;
-      const int half_offset = 2 * classes * coefficient_phases(precision), row_stride = half_offset + 2;
-      if (is_fp32(precision)) {
-        if (elliptic)
-          hipLaunchKernelGGL((strang_snapshot_kernel<float, 1>), dim3(nb), dim3(256), 0, stream, ps, q, half_offset,
-                             row_stride);
-        else
-          hipLaunchKernelGGL((strang_snapshot_kernel<float, 0>), dim3(nb), dim3(256), 0, stream, ps, q, half_offset,
-                             row_stride);
-      } else {
-        if (elliptic)
-          hipLaunchKernelGGL((strang_snapshot_kernel<double, 1>), dim3(nb), dim3(256), 0, stream, ps, q, half_offset,
-                             row_stride);
-        else
-          hipLaunchKernelGGL((strang_snapshot_kernel<double, 0>), dim3(nb), dim3(256), 0, stream, ps, q, half_offset,
-                             row_stride);
-      }
-    } else if (is_fp32(precision)) {
-      hipLaunchKernelGGL((midpoint_snapshot_kernel<float>), dim3(nb), dim3(256), 0, stream, ps, q);
-    } else {
-      hipLaunchKernelGGL((midpoint_snapshot_kernel<double>), dim3(nb), dim3(256), 0, stream, ps, q);
-    }
-  });
+                           const DensityOut& o, hipStream_t stream) {
+  if (base_scheme(scheme) == PD_SCHEME_STRANG) {
+    // per row: (stage classes) x (coefficient phases) pairs, then the half-step pair
+    const int classes = scheme == PD_SCHEME_STRANG4 ? 2 : 1;
+    const int half = 2 * classes * coefficient_phases(precision), stride = half + 2;
+    if (is_fp32(precision))
+      return elliptic ? launch_pass(StrangSnapshot<float, 1>{p, q, half, stride}, p.npts, p.n_out, o, stream)
+                      : launch_pass(StrangSnapshot<float, 0>{p, q, half, stride}, p.npts, p.n_out, o, stream);
+    return elliptic ? launch_pass(StrangSnapshot<double, 1>{p, q, half, stride}, p.npts, p.n_out, o, stream)
+                    : launch_pass(StrangSnapshot<double, 0>{p, q, half, stride}, p.npts, p.n_out, o, stream);
+  }
+  return is_fp32(precision) ? launch_pass(MidpointSnapshot<float>{p, q}, p.npts, p.n_out, o, stream)
+                            : launch_pass(MidpointSnapshot<double>{p, q}, p.npts, p.n_out, o, stream);
 }
 
 // ---------------------------------------------------------------------------
 // Static scratch of the no-allocation density (pd_density_static): the tile partials
-// of one reduction, then its sum.  Each device holds its own copy until the process
+// of one reduction, then its sum, then its blocks' count.  Each device holds its own copy until the process
 // ends; every call on a device shares it.
 
 static_assert(kRedTile * kStaticPartials == kStaticMaxPoints, "static scratch sized for the reduction's tiles");
-static __device__ __align__(256) double scratch[kStaticPartials + 1];
+static __device__ __align__(256) double scratch[kStaticPartials + 2];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -1169,14 +1233,8 @@ hipError_t static_scratch(int device, double** out) {
   return hipSuccess;
 }
 
-hipError_t launch_density(const double* n, long long npts, double scale, double* partial, double* rho,
-                          hipStream_t stream) {
-  long long tiles = density_partials(npts);
-  hipLaunchKernelGGL(density_tiles, dim3((unsigned)tiles), dim3(kRedThreads), 0, stream, n, npts, partial);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(density_finish, dim3(1), dim3(kRedThreads), 0, stream, partial, tiles, scale, rho);
-  return hipGetLastError();
+hipError_t launch_density(const double* n, long long npts, const DensityOut& o, hipStream_t stream) {
+  return launch_pass(StoredDensity{n}, npts, nullptr, o, stream);
 }
 
 hipError_t launch_batch_density(const DensityJob* jobs, int n_jobs, long long total_tiles, hipStream_t stream) {

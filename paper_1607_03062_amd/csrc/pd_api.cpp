@@ -98,6 +98,51 @@ pd_status hip_error(hipError_t e, const char* what) {
   return set_error(PD_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
+namespace {
+constexpr int kSlotsPerPage = 256;
+struct SlotPage {
+  double* base;
+  std::vector<int> free;
+};
+std::mutex g_slots_mu;
+std::vector<SlotPage> g_slot_pages;
+}  // namespace
+
+double* HostSlots::get() {
+  std::lock_guard<std::mutex> lock(g_slots_mu);
+  for (SlotPage& p : g_slot_pages)
+    if (!p.free.empty()) {
+      const int i = p.free.back();
+      p.free.pop_back();
+      return p.base + i;
+    }
+  void* mem = nullptr;
+  if (hipHostMalloc(&mem, kSlotsPerPage * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  SlotPage p{static_cast<double*>(mem), {}};
+  p.free.reserve(kSlotsPerPage);
+  for (int i = kSlotsPerPage - 1; i > 0; --i) p.free.push_back(i);
+  g_slot_pages.push_back(std::move(p));
+  return static_cast<double*>(mem);
+}
+
+void HostSlots::put(double* slot) {
+  if (!slot) return;
+  std::lock_guard<std::mutex> lock(g_slots_mu);
+  for (size_t k = 0; k < g_slot_pages.size(); ++k) {
+    SlotPage& p = g_slot_pages[k];
+    if (slot < p.base || slot >= p.base + kSlotsPerPage) continue;
+    p.free.push_back((int)(slot - p.base));
+    if ((int)p.free.size() == kSlotsPerPage) {
+      (void)hipHostFree(p.base);
+      g_slot_pages.erase(g_slot_pages.begin() + (long)k);
+    }
+    return;
+  }
+}
+
 pd_status mark_use(pd_grid g, hipStream_t stream) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(stream, &cs);
@@ -447,8 +492,10 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   if (!g->d_partial) {
     e = device_malloc(reinterpret_cast<void**>(&g->d_partial), (size_t)density_partials(npts) * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(partials)");
-    e = device_malloc(reinterpret_cast<void**>(&g->d_rho), sizeof(double));
+    e = device_malloc(reinterpret_cast<void**>(&g->d_rho), 2 * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(rho)");
+    if ((e = hipMemset(g->d_rho, 0, 2 * sizeof(double))) != hipSuccess) return hip_fail(e, "hipMemset(rho)");
+    if (!g->h_rho) g->h_rho = HostSlots::get();
   }
   g->field = std::move(t);
   g->n_masked = masked;
@@ -604,32 +651,60 @@ pd_status pd_propagate(pd_grid g, long long max_steps, void* stream) {
 
 namespace {
 
-// Reduce the handle's n buffer into rho and copy the results out (pd_density, pd_snapshot).
-pd_status reduce_and_copy(pd_grid g, double* n_out, int n_out_on_device, double* rho_out, hipStream_t s) {
-  const long long npts = g->grid.points();
-  hipError_t e = launch_density(g->d_n, npts, g->density_scale(), g->d_partial, g->d_rho, s);
-  if (e != hipSuccess) return hip_fail(e, "density launch");
-  bool wait = false;
-  if (n_out) {
-    e = hipMemcpyAsync(n_out, g->d_n, (size_t)npts * sizeof(double),
-                       n_out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "copy of n(p)");
-    wait = !n_out_on_device;
-  }
-  pd_status m = mark_use(g, s);
-  if (m != PD_OK) return m;
+// The end of a density call: the copies the pass did not make, the wait where something goes
+// to the host, and rho from the slot the pass wrote (or, without one, copied from d_rho).
+// The handle's work up to here is then complete, or noted if the call does not wait.
+pd_status finish_density(pd_grid g, const double* d_rho, double* n_out, int n_out_on_device, double* rho_out,
+                         hipStream_t s, bool may_create_event) {
+  hipError_t e;
   double rho = 0.0;
-  if (rho_out) {
-    e = hipMemcpyAsync(&rho, g->d_rho, sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "copy of rho");
-    wait = true;
+  if (n_out && !n_out_on_device) {
+    e = hipMemcpyAsync(n_out, g->d_n, (size_t)g->grid.points() * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (e != hipSuccess) return hip_fail(e, "copy of n(p)");
   }
-  if (wait) {
+  if (rho_out && !g->h_rho) {
+    e = hipMemcpyAsync(&rho, d_rho, sizeof(double), hipMemcpyDeviceToHost, s);
+    if (e != hipSuccess) return hip_fail(e, "copy of rho");
+  }
+  if (may_create_event || g->last_use) {
+    pd_status m = mark_use(g, s);
+    if (m != PD_OK) return m;
+  } else {
+    g->wait_device = true;
+  }
+  if (rho_out || (n_out && !n_out_on_device)) {
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   }
-  if (rho_out) *rho_out = rho;
+  if (rho_out) *rho_out = g->h_rho ? *static_cast<volatile double*>(g->h_rho) : rho;
   return ok();
+}
+
+DensityOut density_out(pd_grid g, double* partial, double* rho, double* n_out, int n_out_on_device) {
+  DensityOut o{};
+  o.partial = partial;
+  o.rho = rho;
+  o.done = reinterpret_cast<unsigned*>(rho + 1);
+  o.rho_host = g->h_rho;
+  o.n_copy = n_out_on_device ? n_out : nullptr;
+  o.scale = g->density_scale();
+  return o;
+}
+
+// pd_density and pd_density_static: the pass over the handle's n buffer with the given
+// scratch.  Without a rho to return it is a copy of n.
+pd_status density_call(pd_grid g, double* partial, double* rho, double* n_out, int n_out_on_device, double* rho_out,
+                       hipStream_t s, bool may_create_event) {
+  const long long npts = g->grid.points();
+  hipError_t e = hipSuccess;
+  if (rho_out) {
+    e = launch_density(g->d_n, npts, density_out(g, partial, rho, n_out, n_out_on_device), s);
+    if (e != hipSuccess) return hip_fail(e, "density launch");
+  } else if (n_out && n_out_on_device) {
+    e = hipMemcpyAsync(n_out, g->d_n, (size_t)npts * sizeof(double), hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return hip_fail(e, "copy of n(p)");
+  }
+  return finish_density(g, rho, n_out, n_out_on_device, rho_out, s, may_create_event);
 }
 
 }  // namespace
@@ -642,7 +717,8 @@ pd_status pd_density(pd_grid g, double* n_out, int n_out_on_device, double* rho_
                 g->field_set ? g->field.n_steps : 0LL);
   DeviceScope scope(g->device);
   if (!scope.ok) return fail(PD_ERR_DEVICE, "cannot select device %d", g->device);
-  return reduce_and_copy(g, n_out, n_out_on_device, rho_out, static_cast<hipStream_t>(stream));
+  return density_call(g, g->d_partial, g->d_rho, n_out, n_out_on_device, rho_out, static_cast<hipStream_t>(stream),
+                      true);
 }
 
 pd_status pd_density_static(pd_grid g, double* n_out, int n_out_on_device, double* rho_out, void* stream) {
@@ -660,39 +736,12 @@ pd_status pd_density_static(pd_grid g, double* n_out, int n_out_on_device, doubl
   double* sc = nullptr;
   hipError_t e = static_scratch(g->device, &sc);
   if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  // partials in sc[0 .. tiles), the sum in sc[kStaticPartials]; every partial is
-  // written before it is read, so nothing needs clearing
-  e = launch_density(g->d_n, npts, g->density_scale(), sc, sc + kStaticPartials, s);
-  if (e != hipSuccess) return hip_fail(e, "density launch");
-  bool wait = false;
-  if (n_out) {
-    e = hipMemcpyAsync(n_out, g->d_n, (size_t)npts * sizeof(double),
-                       n_out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "copy of n(p)");
-    wait = !n_out_on_device;
-  }
-  // the handle's completion event exists once a propagation was enqueued outside
-  // capture; otherwise a later pd_set_field waits for the device (creating an event
-  // here could allocate)
-  if (g->last_use) {
-    pd_status m = mark_use(g, s);
-    if (m != PD_OK) return m;
-  } else {
-    g->wait_device = true;
-  }
-  double rho = 0.0;
-  if (rho_out) {
-    e = hipMemcpyAsync(&rho, sc + kStaticPartials, sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "copy of rho");
-    wait = true;
-  }
-  if (wait) {
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  }
-  if (rho_out) *rho_out = rho;
-  return ok();
+  // partials in sc[0 .. tiles), the sum in sc[kStaticPartials], then the count of the
+  // pass's blocks, 0 between passes.  The handle's completion event exists once a
+  // propagation was enqueued outside capture; otherwise a later pd_set_field waits for
+  // the device (creating an event here could allocate).
+  return density_call(g, sc, sc + kStaticPartials, n_out, n_out_on_device, rho_out, static_cast<hipStream_t>(stream),
+                      false);
 }
 
 pd_status pd_snapshot(pd_grid g, double* n_out, int n_out_on_device, double* rho_out, void* stream) {
@@ -721,10 +770,12 @@ pd_status pd_snapshot(pd_grid g, double* n_out, int n_out_on_device, double* rho
       double half = g->vsign() * 0.5 * g->field.dt * (g->field.comp.c[0] * g->field.Ay_mid[(size_t)(k * S)]);
       rotation_coefficients(-half, g->form, &q.undo_a, &q.undo_s);
     }
-    hipError_t e = launch_snapshot(g->scheme, g->precision, g->field.elliptic ? 1 : 0, p, q, s);
+    hipError_t e = launch_snapshot(g->scheme, g->precision, g->field.elliptic ? 1 : 0, p, q,
+                                   density_out(g, g->d_partial, g->d_rho, n_out, n_out_on_device), s);
     if (e != hipSuccess) return hip_fail(e, "snapshot launch");
+    return finish_density(g, g->d_rho, n_out, n_out_on_device, rho_out, s, true);
   }
-  return reduce_and_copy(g, n_out, n_out_on_device, rho_out, s);
+  return density_call(g, g->d_partial, g->d_rho, n_out, n_out_on_device, rho_out, s, true);
 }
 
 pd_status pd_get_info(pd_grid g, pd_info* out) {
@@ -746,6 +797,7 @@ void pd_destroy_grid(pd_grid g) {
     release(g->d_n);
     release(g->d_partial);
     release(g->d_rho);
+    HostSlots::put(g->h_rho);
     release(g->d_state_own);
     if (g->last_use) (void)hipEventDestroy(g->last_use);
   }

@@ -285,16 +285,26 @@ struct DensityJob {
 // kernels.hip
 hipError_t launch_propagate(int scheme, int precision, int points_per_lane, int block_threads, int taylor,
                             int elliptic, const SolveParams& p, hipStream_t stream);
+// What a density pass writes beside n: its tile sums, rho on the device and (if not null)
+// in page-locked host memory, a copy of n (if not null).  `done`: the blocks' count, 0
+// between passes.
+struct DensityOut {
+  double* partial;
+  unsigned* done;
+  double* rho;
+  double* rho_host;
+  double* n_copy;
+  double scale;
+};
 hipError_t launch_snapshot(int scheme, int precision, int elliptic, const SolveParams& p, const SnapshotParams& q,
-                           hipStream_t stream);
-hipError_t launch_density(const double* n, long long npts, double scale, double* partial, double* rho,
-                          hipStream_t stream);
+                           const DensityOut& o, hipStream_t stream);
+hipError_t launch_density(const double* n, long long npts, const DensityOut& o, hipStream_t stream);
 // Largest grid the static scratch of pd_density_static serves, and the tile
 // partials it holds for it (the density reduction sums tiles of 2048 points).
 constexpr long long kStaticMaxPoints = 1LL << 28;
 constexpr long long kStaticPartials = kStaticMaxPoints / 2048;
 // Device address of the static scratch on `device` (kStaticPartials partials, then
-// one sum), looked up on the first call for that device.
+// one sum and the pass's block count), looked up on the first call for that device.
 hipError_t static_scratch(int device, double** out);
 // The persistent kernels of a batch: tiles of the row kernel, and waves' units of the
 // column kernels.  Each has its own work items and its own counter.
@@ -338,7 +348,8 @@ struct pd_grid_s {
   size_t col_offset = 0, row_offset = 0;
   double* d_n = nullptr;
   double* d_partial = nullptr;
-  double* d_rho = nullptr;
+  double* d_rho = nullptr;    // the sum, then the count of the density pass's blocks
+  double* h_rho = nullptr;    // where the device leaves rho for the host (HostSlots)
   void* d_state_own = nullptr;
   void* d_state_bound = nullptr;
   size_t state_bound_bytes = 0;
@@ -382,6 +393,15 @@ struct pd_grid_s {
 };
 
 namespace pdx {
+// Doubles of page-locked host memory that kernels write and the host reads, handed out from
+// pages that the process's handles share (a page-locked allocation of its own for each would
+// cost more than a small solve); a page is freed when its last slot is given back.  Safe from
+// several threads.  get: null if no page can be allocated.
+struct HostSlots {
+  static double* get();
+  static void put(double* slot);
+};
+
 // Makes a device current for the lifetime of the scope.
 struct DeviceScope {
   int prev = -1;

@@ -1,0 +1,49 @@
+"""The density pass at the sizes where its tiles of 2048 points and its two ways to sum them
+(the last of up to 256 blocks, or a second launch) change over: rho against the sum of the
+returned n, the copies of n to device and host memory, and the same bits from every way to
+call it.  The sum of n is exact to a rounding per addition: 1e-14 relative, as elsewhere.
+"""
+import math
+
+import numpy as np
+import pytest
+
+from paper_1607_03062_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (23, 89), (32, 64), (683, 3), (1024, 512), (1025, 512)])
+@pytest.mark.parametrize("scheme,precision", [("strang", "fp64"), ("strang", "fp32"), ("midpoint", "fp64")])
+def test_density_and_snapshot(gpu, nx, ny, scheme, precision):
+    import torch
+
+    g = {"nx": nx, "ny": ny, "px": (-1.3, 1.2), "py": (-1.1, 1.4)}
+    s = gpu.Solver.for_grid(g, precision, scheme).set_field(wl.sin2(0.3, 0.6, 2), 200)
+    scale = 4 * (2.5 / nx) * (2.5 / ny) / (4 * math.pi ** 2)
+    st = torch.cuda.Stream()
+
+    def both(call):
+        """rho and n of a call with n to the device and with n to the host; they agree."""
+        dev, host = torch.empty(nx * ny, dtype=torch.float64, device="cuda"), np.empty(nx * ny)
+        rho = call(dev, st)
+        assert call(host, st) == rho and call(None, st) == rho
+        st.synchronize()
+        assert np.array_equal(dev.cpu().numpy(), host)
+        want = scale * math.fsum(host)
+        assert abs(rho - want) <= 1e-14 * want
+        return rho, host
+
+    s.propagate(90, stream=st)
+    both(lambda n, t: s.snapshot(n_out=n, stream=t))
+    s.propagate(-1, stream=st)
+    end = both(lambda n, t: s.density(n_out=n, stream=t))
+    static = both(lambda n, t: s.density_static(n_out=n, stream=t))
+    last = both(lambda n, t: s.snapshot(n_out=n, stream=t))
+    for other in (static, last):
+        assert other[0] == end[0] and np.array_equal(other[1], end[1])
+    only_n = torch.empty(nx * ny, dtype=torch.float64, device="cuda")
+    assert s.density(n_out=only_n, want_rho=False, stream=st) is None
+    st.synchronize()
+    assert np.array_equal(only_n.cpu().numpy(), end[1])
+    s.close()
