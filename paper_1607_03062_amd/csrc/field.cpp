@@ -5,7 +5,9 @@
 // Gauge A_0 = 0, E = -dA/dt, A(t) = -int_{t_i}^{t} E (Sec. II, after Eq. (2));
 // A is sampled at the step midpoints t_i + (k + 1/2) dt (Sec. III, Eqs. (11)-(12)),
 // or for the fourth-order composition at the stage midpoints t_i + (k + sigma_j) dt.
+#include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 
 #include "pd_internal.h"
@@ -107,6 +109,216 @@ void eval_A(const pd_field& f, double t, double* ax, double* ay) {
   }
 }
 
+// A component of A over [begin, end] as c0 + lin t + sum_i amp_i f(freq_i t + phase_i), f the
+// sine or its square: what an analytic field is between the corners of its envelope.  Many
+// samples of it are evaluated side by side (sample_span).
+struct SineSum {
+  double end = 0, c0 = 0, lin = 0;
+  bool squared = false;
+  int n = 0;
+  double amp[3] = {}, freq[3] = {}, phase[3] = {};
+  void add(double a, double w, double q) {
+    amp[n] = a;
+    freq[n] = w;
+    phase[n++] = q;
+  }
+  // c0 such that the value at t is `value`
+  void pass_through(double t, double value) {
+    double v = lin * t;
+    for (int i = 0; i < n; ++i) v += amp[i] * std::sin(freq[i] * t + phase[i]);
+    c0 = value - v;
+  }
+};
+
+// pi in three parts of 33, 33 and 53 bits: a multiple below 2^20 of the first two is exact.
+constexpr double kPiA = 0x1.921fb54400000p+1, kPiB = 0x1.0b4611a600000p-33, kPiC = 0x1.3198a2e037073p-68;
+
+// sin x to 4e-16 for |x| < 2^20 (the samples' arguments are rounded by far more): x less the nearest multiple k pi,
+// the Taylor series to x^23 (its next term is 5e-21 at pi/2), the sign of an odd k.  Without
+// branches or library calls, so that a loop over it runs in vector registers.
+inline __attribute__((always_inline)) double sin_lane(double x) {
+  constexpr double kMagic = 0x1.8p52;  // adding it rounds to a whole number, in its low bits
+  const double m = x * (1.0 / kPi) + kMagic, k = m - kMagic;
+  const double r = ((x - k * kPiA) - k * kPiB) - k * kPiC, z = r * r;
+  // in pairs, pairs of pairs and so on: short chains, which loops over it overlap
+  const double z2 = z * z, z4 = z2 * z2, z8 = z4 * z4;
+  const double p0 = -1.0 / 6.0 + z * (1.0 / 120.0), p1 = -1.0 / 5040.0 + z * (1.0 / 362880.0);
+  const double p2 = -1.0 / 39916800.0 + z * (1.0 / 6227020800.0);
+  const double p3 = -1.0 / 1307674368000.0 + z * (1.0 / 355687428096000.0);
+  const double p4 = -1.0 / 121645100408832000.0 + z * (1.0 / 51090942171709440000.0);
+  const double p = ((p0 + z2 * p1) + z4 * (p2 + z2 * p3)) + z8 * (p4 - z2 * (1.0 / 25852016738884976640000.0));
+  const double v = r + r * (z * p);
+  uint64_t odd, bits;
+  std::memcpy(&odd, &m, sizeof odd);
+  std::memcpy(&bits, &v, sizeof bits);
+  bits ^= odd << 63;
+  double out;
+  std::memcpy(&out, &bits, sizeof out);
+  return out;
+}
+constexpr double kSinLaneMax = 0x1p20;
+
+// out[i * stride] = the component at t0 + (first + i + sigma) dt, i < n <= kSpan.
+constexpr int kSpan = 256;
+inline __attribute__((always_inline)) void span_body(const SineSum& f, double t0, double first, double sigma,
+                                                     double dt, int n, double* out, int stride) {
+  double t[kSpan], v[kSpan];
+  for (int i = 0; i < n; ++i) {
+    t[i] = t0 + ((first + (double)i) + sigma) * dt;
+    v[i] = f.c0 + f.lin * t[i];
+  }
+  for (int q = 0; q < f.n; ++q) {
+    const double a = f.amp[q], w = f.freq[q], p = f.phase[q];
+    if (f.squared)
+      for (int i = 0; i < n; ++i) {
+        const double y = sin_lane(w * t[i] + p);
+        v[i] += a * (y * y);
+      }
+    else
+      for (int i = 0; i < n; ++i) v[i] += a * sin_lane(w * t[i] + p);
+  }
+  for (int i = 0; i < n; ++i) out[(size_t)i * stride] = v[i];
+}
+// Twice, for four and for two doubles to a register.  Neither contracts a multiply and an
+// add (no FMA in the target, -ffp-contract=off), so both give the same values.
+__attribute__((target("avx2"))) void span_avx2(const SineSum& f, double t0, double first, double sigma, double dt,
+                                               int n, double* out, int stride) {
+  span_body(f, t0, first, sigma, dt, n, out, stride);
+}
+void span_base(const SineSum& f, double t0, double first, double sigma, double dt, int n, double* out, int stride) {
+  span_body(f, t0, first, sigma, dt, n, out, stride);
+}
+void span(const SineSum& f, double t0, double first, double sigma, double dt, int n, double* out, int stride) {
+  static const bool avx2 = __builtin_cpu_supports("avx2");
+  (avx2 ? span_avx2 : span_base)(f, t0, first, sigma, dt, n, out, stride);
+}
+
+// The pieces of a component of an analytic field (validated), in time order.
+int pieces_of(const pd_field& f, bool y, SineSum out[3]) {
+  switch (f.kind) {
+    case PD_FIELD_SIN2: {
+      // see Sin2Pulse
+      const double T = f.cycles * 2.0 * kPi / f.omega, W = 2.0 * kPi / T, w = f.omega;
+      SineSum& p = out[0];
+      p.end = T;
+      if (y) {
+        const double a = -f.ellipticity * f.E0;
+        p.add(a / (2.0 * w), w, 0.0);
+        p.add(-a / (4.0 * (w + W)), w + W, 0.0);
+        p.add(-a / (4.0 * (w - W)), w - W, 0.0);
+      } else {
+        p.squared = true;
+        p.add(-f.E0 / w, 0.5 * w, 0.0);
+        p.add(f.E0 / (2.0 * (w + W)), 0.5 * (w + W), 0.0);
+        p.add(f.E0 / (2.0 * (w - W)), 0.5 * (w - W), 0.0);
+      }
+      return 1;
+    }
+    case PD_FIELD_CONSTANT:
+      out[0].end = f.t_end;
+      out[0].lin = y ? -f.ellipticity * f.E0 : -f.E0;
+      return 1;
+    default: {
+      // see LaserPulse: rise, flat, fall, each a carrier with or without its two side bands
+      const double a = y ? f.ellipticity * f.E0 : f.E0, q = y ? f.phi - 0.5 * kPi : f.phi, w = f.omega;
+      const LaserPulse lp{f.E0, w, f.phi, f.omega_rise, f.omega_fall, f.duration};
+      const double ends[3] = {lp.tr(), lp.ta(), lp.D};
+      double t = 0.0, value = 0.0;
+      int m = 0;
+      for (int part = 0; part < 3; ++part) {
+        if (!(ends[part] > t)) continue;  // no flat part
+        SineSum& p = out[m++];
+        p.end = ends[part];
+        if (part == 1) {
+          p.add(-a / w, w, q);
+        } else {
+          // the side bands of cos(2 W (t - c)) cos(w t + q), subtracted in the rise and added in the fall
+          const double W = part == 0 ? lp.Wr : lp.Wf, c = part == 0 ? 0.0 : lp.ta(), sign = part == 0 ? 0.25 : -0.25;
+          const double w1 = w + 2.0 * W, w2 = w - 2.0 * W;
+          p.add(-0.5 * a / w, w, q);
+          p.add(sign * a / w1, w1, q - 2.0 * W * c);
+          if (w2 != 0.0)
+            p.add(sign * a / w2, w2, q + 2.0 * W * c);
+          else
+            p.lin = sign * a * std::cos(q + 2.0 * W * c);
+        }
+        p.pass_through(t, value);
+        t = p.end;
+        value = (y ? f.ellipticity * lp.A_phase(q, t) : lp.A_phase(q, t));
+      }
+      return m;
+    }
+  }
+}
+
+// Samples [k0, k1) of every stage of one component into `out` (stage stride S).
+void sample_component(const pd_field& f, bool y, double t_i, double dt, const Composition& comp, long long k0,
+                      long long k1, double* out) {
+  SineSum p[3];
+  const int m = pieces_of(f, y, p);
+  const int S = comp.stages;
+  bool in_range = true;
+  for (int i = 0; i < m; ++i)
+    for (int q = 0; q < p[i].n; ++q)
+      in_range = in_range && std::fabs(p[i].freq[q]) * p[i].end + std::fabs(p[i].phase[q]) < kSinLaneMax;
+  for (int j = 0; j < S; ++j) {
+    const auto time = [&](long long k) { return t_i + ((double)k + comp.sigma[j]) * dt; };
+    long long k = k0;
+    for (int i = 0; i < m && k < k1; ++i) {
+      // the samples up to the piece's end (the last piece takes the rest)
+      long long e = k1;
+      if (i + 1 < m) {
+        e = std::min(k1, std::max(k, (long long)((p[i].end - t_i) / dt - comp.sigma[j])));
+        while (e < k1 && time(e) <= p[i].end) ++e;
+        while (e > k && time(e - 1) > p[i].end) --e;
+      }
+      for (; k < e; k += kSpan) {
+        const int n = (int)std::min<long long>(kSpan, e - k);
+        if (in_range) {
+          span(p[i], t_i, (double)k, comp.sigma[j], dt, n, out + (size_t)k * S + j, S);
+        } else {
+          double ax, ay;
+          for (int v = 0; v < n; ++v) {
+            eval_A(f, time(k + v), &ax, &ay);
+            out[(size_t)(k + v) * S + j] = y ? ay : ax;
+          }
+        }
+      }
+      k = e;
+    }
+  }
+}
+
+// Whether every value is finite, and the range of the values with what *lo, *hi hold.
+bool value_range(const std::vector<double>& v, double* lo, double* hi) {
+  constexpr int kLanes = 8;
+  double a[kLanes], b[kLanes], bad = 0.0;
+  for (int i = 0; i < kLanes; ++i) {
+    a[i] = *lo;
+    b[i] = *hi;
+  }
+  const size_t n = v.size(), whole = n / kLanes * kLanes;
+  double nan[kLanes] = {};
+  for (size_t i = 0; i < whole; i += kLanes)
+    for (int q = 0; q < kLanes; ++q) {
+      const double x = v[i + q];
+      a[q] = x < a[q] ? x : a[q];
+      b[q] = x > b[q] ? x : b[q];
+      nan[q] += x - x;  // 0 for a finite value, else NaN from here on
+    }
+  for (size_t i = whole; i < n; ++i) {
+    a[0] = v[i] < a[0] ? v[i] : a[0];
+    b[0] = v[i] > b[0] ? v[i] : b[0];
+    bad += v[i] - v[i];
+  }
+  for (int q = 0; q < kLanes; ++q) {
+    bad += nan[q];
+    *lo = a[q] < *lo ? a[q] : *lo;
+    *hi = b[q] > *hi ? b[q] : *hi;
+  }
+  return bad == 0.0;
+}
+
 }  // namespace
 
 Composition composition_of(int scheme) {
@@ -140,6 +352,8 @@ bool sample_field(const pd_field& f, long long n_steps, const Composition& comp,
   const int S = comp.stages;
   const size_t n_samples = (size_t)n_steps * (size_t)S;
   FieldTables t;
+  t.A_mid = std::move(out->A_mid);  // the buffers of what *out holds, used again
+  t.Ay_mid = std::move(out->Ay_mid);
   t.n_steps = n_steps;
   t.comp = comp;
   t.spec = f;
@@ -210,7 +424,7 @@ bool sample_field(const pd_field& f, long long n_steps, const Composition& comp,
   t.dt = (t.t_f - t.t_i) / (double)n_steps;
   t.elliptic = f.kind == PD_FIELD_TABLE ? f.Ay_mid != nullptr : f.ellipticity != 0.0;
   t.A_mid.resize(n_samples);
-  if (t.elliptic) t.Ay_mid.resize(n_samples);
+  t.Ay_mid.resize(t.elliptic ? n_samples : 0);
   if (f.kind == PD_FIELD_TABLE) {
     std::memcpy(t.A_mid.data(), f.A_mid, n_samples * sizeof(double));
     if (t.elliptic) std::memcpy(t.Ay_mid.data(), f.Ay_mid, n_samples * sizeof(double));
@@ -219,39 +433,22 @@ bool sample_field(const pd_field& f, long long n_steps, const Composition& comp,
     t.Ay_in = t.elliptic ? f.Ay_in : 0.0;
     t.Ay_out = t.elliptic ? f.Ay_out : 0.0;
   } else {
-    parallel_ranges(n_steps, 8192, [&](long long k0, long long k1) {
-      double ax, ay;
-      for (long long k = k0; k < k1; ++k)
-        for (int j = 0; j < S; ++j) {
-          eval_A(f, t.t_i + ((double)k + comp.sigma[j]) * t.dt, &ax, &ay);
-          t.A_mid[(size_t)k * S + j] = ax;
-          if (t.elliptic) t.Ay_mid[(size_t)k * S + j] = ay;
-        }
+    // a thread is worth its start for some 30000 samples (3 ns each)
+    parallel_ranges(n_steps, 32768 / S, [&](long long k0, long long k1) {
+      sample_component(f, false, t.t_i, t.dt, comp, k0, k1, t.A_mid.data());
+      if (t.elliptic) sample_component(f, true, t.t_i, t.dt, comp, k0, k1, t.Ay_mid.data());
     });
     eval_A(f, t.t_i, &t.A_in, &t.Ay_in);
     eval_A(f, t.t_f, &t.A_out, &t.Ay_out);
   }
-  for (double a : t.A_mid)
-    if (!finite(a)) {
-      *err = "field has a non-finite value";
-      return false;
-    }
-  for (double a : t.Ay_mid)
-    if (!finite(a)) {
-      *err = "field has a non-finite value";
-      return false;
-    }
   t.A_min = std::fmin(t.A_in, t.A_out);
   t.A_max = std::fmax(t.A_in, t.A_out);
-  for (double a : t.A_mid) {
-    t.A_min = std::fmin(t.A_min, a);
-    t.A_max = std::fmax(t.A_max, a);
-  }
   t.Ay_min = std::fmin(t.Ay_in, t.Ay_out);
   t.Ay_max = std::fmax(t.Ay_in, t.Ay_out);
-  for (double a : t.Ay_mid) {
-    t.Ay_min = std::fmin(t.Ay_min, a);
-    t.Ay_max = std::fmax(t.Ay_max, a);
+  const bool x_ok = value_range(t.A_mid, &t.A_min, &t.A_max), y_ok = value_range(t.Ay_mid, &t.Ay_min, &t.Ay_max);
+  if (!x_ok || !y_ok) {
+    *err = "field has a non-finite value";
+    return false;
   }
   if (!finite(t.A_min) || !finite(t.A_max) || !finite(t.Ay_min) || !finite(t.Ay_max) || !(t.dt > 0.0)) {
     *err = "field sampling produced non-finite values";
@@ -362,17 +559,22 @@ void build_step_table(const FieldTables& t, int scheme, int precision, int form,
   if (columns) {
     // half angles in FP64: per stage c_j dt A_x, then those of the y rotations' field parts
     const size_t V = (size_t)S * (ell ? 2 : 1);
-    rows->assign((size_t)R * V * sizeof(double), 0);
+    rows->resize((size_t)R * V * sizeof(double));
     double* d = reinterpret_cast<double*>(rows->data());
-    for (long long k = 0; k < N; ++k)
-      for (int j = 0; j < S; ++j) {
-        d[(size_t)k * V + j] = vsign * (c[j] * t.dt) * t.A_mid[(size_t)k * S + j];
-        if (ell) d[(size_t)k * V + S + j] = y_half(k, j);
-      }
-    if (ell) d[(size_t)N * V + S] = open;
+    for (int j = 0; j < S; ++j) {
+      const double scale = vsign * (c[j] * t.dt);
+      for (long long k = 0; k < N; ++k) d[(size_t)k * V + j] = scale * t.A_mid[(size_t)k * S + j];
+    }
+    if (ell) {
+      for (long long k = 0; k < N; ++k)
+        for (int j = 0; j < S; ++j) d[(size_t)k * V + S + j] = y_half(k, j);
+      std::fill_n(d + (size_t)N * V, V, 0.0);
+      d[(size_t)N * V + S] = open;
+    }
     return;
   }
-  rows->assign((size_t)R * table_row_bytes(scheme, precision, ell), 0);
+  rows->resize((size_t)R * table_row_bytes(scheme, precision, ell));
+  std::fill(rows->end() - (std::ptrdiff_t)table_row_bytes(scheme, precision, ell), rows->end(), 0);
   if (base_scheme(scheme) == PD_SCHEME_MIDPOINT) {
     // per stage the phase increment c_j dt A at the stage midpoint (then c_j dt A_y)
     double* d = reinterpret_cast<double*>(rows->data());
@@ -425,11 +627,16 @@ void dither(double x, int phases, float* out) {
     for (int h = 0; h < phases; ++h) out[h] = -out[h];
     return;
   }
-  float lo = (float)x;
-  if ((double)lo > x) lo = std::nextafter(lo, -INFINITY);
-  const float hi = std::nextafter(lo, INFINITY);
+  // neighbours of a float >= 0 differ by one in their bits
+  float lo = (float)x, hi;
+  uint32_t bits;
+  std::memcpy(&bits, &lo, sizeof bits);
+  if ((double)lo > x) --bits;
+  std::memcpy(&lo, &bits, sizeof bits);
+  ++bits;
+  std::memcpy(&hi, &bits, sizeof bits);
   const double f = (x - (double)lo) / ((double)hi - (double)lo);
-  const int up = (int)std::lround(f * phases);
+  const int up = (int)(f * phases + 0.5);
   for (int h = 0; h < phases; ++h) {
     // rank of phase h in the bit-reversed order of the cycle
     int r = 0;

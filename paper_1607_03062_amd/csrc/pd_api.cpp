@@ -446,13 +446,15 @@ pd_status pd_set_valley(pd_grid g, int valley) {
 pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   TraceCall trace("pd_set_field");
   FieldTables t;
+  if (g) t = std::move(g->spare_field);
   long long masked = 0;
   int taylor = 0, form = 0;
   pd_status s = prepare_field(g, f, n_steps, &t, &masked, &taylor, &form);
   if (s != PD_OK) return s;
   const bool strang = base_scheme(g->scheme) == PD_SCHEME_STRANG;
   const int series = strang ? column_series(g->grid, t, g->precision) : 0;
-  std::vector<unsigned char> rows;
+  std::vector<unsigned char>& rows = g->upload;
+  rows.clear();
   build_step_table(t, g->scheme, g->precision, form, series != 0, g->vsign(), &rows);
   size_t col_offset = 0, row_offset = 0;
   if (strang)
@@ -497,6 +499,7 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
     if ((e = hipMemset(g->d_rho, 0, 2 * sizeof(double))) != hipSuccess) return hip_fail(e, "hipMemset(rho)");
     if (!g->h_rho) g->h_rho = HostSlots::get();
   }
+  g->spare_field = std::move(g->field);
   g->field = std::move(t);
   g->n_masked = masked;
   g->taylor = taylor;

@@ -333,6 +333,9 @@ struct pd_grid_s {
 
   bool field_set = false;
   pdx::FieldTables field;
+  // host buffers of the last field but one and of the upload, kept for the next field
+  pdx::FieldTables spare_field;
+  std::vector<unsigned char> upload;
   long long n_masked = 0;
   long long steps_done = 0;
   int taylor = 0;

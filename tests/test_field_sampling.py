@@ -1,0 +1,38 @@
+"""The library's side-by-side sampling of the analytic fields at the sizes and pulse shapes
+where its blocks of 256 samples and its pieces (rise, flat, fall) change over, against the
+oracle.  4e-15 of the field's scale, as for the other sampling tests; past a phase of 2^20,
+where single samples are evaluated instead, the rounding of the phase itself."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1607_03062_amd import _lib
+
+PULSE = {"kind": "pulse", "E0": 0.8, "omega": 0.5, "phi": 0.4, "omega_rise": 0.07, "omega_fall": 0.11,
+         "duration": 60.0, "ellipticity": 0.6}
+FIELDS = {
+    "sin2": {"kind": "sin2", "E0": 0.3, "omega": 0.4, "cycles": 3, "ellipticity": 0.5},
+    "sin2_two_cycles": {"kind": "sin2", "E0": 0.3, "omega": 0.4, "cycles": 2, "ellipticity": -0.5},
+    "constant": {"kind": "constant", "E0": 0.2, "t_end": 31.0, "ellipticity": 0.3},
+    "pulse": PULSE,
+    "pulse_no_flat_part": dict(PULSE, duration=np.pi / 0.14 + np.pi / 0.22),
+    "pulse_resonant_rise": dict(PULSE, omega=0.14),  # the lower side band of the rise at zero frequency
+    "pulse_resonant_fall": dict(PULSE, omega=0.22),
+}
+
+
+@pytest.mark.parametrize("N", [1, 2, 7, 255, 256, 257, 1000, 40000])
+@pytest.mark.parametrize("kind", sorted(FIELDS))
+@pytest.mark.parametrize("scheme", ["strang", "strang4"])
+def test_samples_match_the_oracle(kind, N, scheme):
+    f = FIELDS[kind]
+    Ax, Ay, _ = _lib.sample_field_xy(f, N, scheme)
+    ox, oy = oracle.field_table(f, N, scheme)[0], oracle.field_table_y(f, N, scheme)[0]
+    scale = max(1.0, np.abs(ox).max(), np.abs(oy).max())
+    assert np.max(np.abs(Ax - ox)) <= 4e-15 * scale and np.max(np.abs(Ay - oy)) <= 4e-15 * scale
+
+
+def test_large_phases():
+    f = dict(PULSE, phi=3e6, ellipticity=0.0)
+    Ax = _lib.sample_field_xy(f, 500, "strang")[0]
+    assert np.max(np.abs(Ax - oracle.field_table(f, 500, "strang")[0])) <= 8 * 3e6 * 2.0 ** -52
