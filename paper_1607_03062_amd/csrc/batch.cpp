@@ -149,17 +149,22 @@ long long persistent_slots(pd_batch b, int kind) {
   return b->slots[kind];
 }
 
-// Members the persistent kernels run: second-order Strang, no y component, with
-// fewer tiles than the kernel has resident blocks.  A member with at least that many tiles
-// fills the device by itself; its own launch (its grid's shape, blocks scheduled by
-// the hardware) then runs at the rate of the solve alone, where the persistent
-// kernel's equal items would leave a partly filled last round of blocks (a lone
-// 2048^2 member in a 3000-step epoch ran at 0.90 of that rate, against 0.96 in its
-// own launch).
+// Members the persistent kernels run: second-order Strang, no y component, with fewer tiles
+// than the row kernel has resident blocks, or twice as many as the column kernel has.  A
+// member with more fills the device by itself; its own launch (its grid's shape, blocks
+// scheduled by the hardware) then runs at the rate of the solve alone, where the persistent
+// kernel's equal items would leave a partly filled last round of blocks (rows: a lone
+// 2048^2 member in a 3000-step epoch ran at 0.90 of that rate, against 0.96 in its own
+// launch).  By columns a 1024^2 member, 1024 tiles for 1024 resident blocks, is as fast
+// among the items as by itself (epochs of 3000 steps, own / among: alone 0.57 / 0.57 ms, with
+// three small members 0.86 / 0.74), and whole solves of three of them and thirteen smaller
+// ones pack better: 3.70 / 3.35 ms.
 bool persistent_member(pd_batch b, pd_grid g) {
   if (g->scheme != PD_SCHEME_STRANG || g->field.elliptic) return false;
   long long span;
-  return g->batch_tiles(b->points_per_lane, b->block_threads, &span) < persistent_slots(b, batch_kind(g));
+  const int kind = batch_kind(g);
+  const long long most = persistent_slots(b, kind) * (kind == kBatchColumns ? 2 : 1);
+  return g->batch_tiles(b->points_per_lane, b->block_threads, &span) < most;
 }
 
 // Descriptors for advancing member i over steps [begin[i], end[i]) (no work
