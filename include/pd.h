@@ -159,7 +159,7 @@ typedef struct {
                                Midpoint: 0 = tangent form (the step divided by cos(dt E), one
                                series; chosen when the state's growth over 1024 steps stays
                                below 2^32), 1 = cosine form (cos - 1 and sin(x)/x) */
-  int taylor_order;         /* midpoint: terms J of the series (tan(x)/x, or cos - 1 and
+  int taylor_order;         /* midpoint: Taylor terms that reach the precision (tan(x)/x, or cos - 1 and
                                sin(x)/x) in x = (c dt E)^2 */
   size_t device_bytes;      /* device memory the handle owns (its table allocation may exceed the current table) */
   size_t solve_bytes;       /* device memory a solve of this field needs, chunk state included:

@@ -851,6 +851,55 @@ int taylor_order(double x_max, int precision, int form) {
   return -1;
 }
 
+TanPolynomial tan_polynomial(double x_max, int precision) {
+  static const int k64[] = {4, 5, 6, 8}, k32[] = {2, 3, 4, 5};
+  const bool f32 = is_fp32(precision);
+  const double tol = f32 ? 0x1p-30 : 0x1p-58;
+  const int* orders = f32 ? k32 : k64;
+  const int count = 4;
+  // q(x) = sum_{k >= 0} b_k x^k, b_k = a_{k+2}, to the terms that double precision holds for
+  // the angles of the tangent form
+  constexpr int kTerms = 26;
+  long double b[kTerms];
+  for (int k = 0; k < kTerms; ++k) b[k] = tan_series_coef(k + 2);
+  TanPolynomial p{};
+  const int taylor = taylor_order(x_max, precision, kMidTangent);
+  for (int o = 0; o < count; ++o) {
+    const int J = orders[o], m = J - 2;  // q by a polynomial of degree m
+    p.terms = J;
+    double r = 4.0 * x_max / (kPi * kPi);
+    for (int n = 2; n <= J; ++n) p.c[n] = tan_series_coef(n);
+    if (tan_series_coef(J + 1) * std::pow(x_max, J) / (1.0 - r) <= tol) return p;
+    // Chebyshev nodes: |q - polynomial| <= max |q^(m+1)| / (m+1)! (x_max / 4)^(m+1) 2, and all
+    // derivatives of q grow with x
+    long double deriv = 0, binom = 1, power = 1;  // C(k, m+1) x_max^(k-m-1)
+    for (int k = m + 1; k < kTerms; ++k) {
+      deriv += binom * b[k] * power;
+      binom = binom * (k + 1) / (k - m);
+      power *= x_max;
+    }
+    const double bound = (double)(deriv * std::pow(0.25L * x_max, m + 1) * 2.0L * x_max);
+    if (bound > tol && J == taylor) return p;
+    if (bound > tol && o + 1 < count) continue;
+    // Newton's divided differences at the nodes, expanded
+    long double node[kTanTermsMax], diff[kTanTermsMax], c[kTanTermsMax] = {};
+    for (int i = 0; i <= m; ++i) {
+      node[i] = 0.5L * x_max * (1.0L + std::cos((2 * i + 1) * 3.14159265358979323846L / (2 * m + 2)));
+      diff[i] = 0;
+      for (int k = kTerms - 1; k >= 0; --k) diff[i] = diff[i] * node[i] + b[k];
+    }
+    for (int w = 1; w <= m; ++w)
+      for (int i = m; i >= w; --i) diff[i] = (diff[i] - diff[i - 1]) / (node[i] - node[i - w]);
+    for (int i = m; i >= 0; --i) {
+      for (int k = m; k >= 1; --k) c[k] = c[k - 1] - node[i] * c[k];
+      c[0] = diff[i] - node[i] * c[0];
+    }
+    for (int k = 0; k <= m; ++k) p.c[k + 2] = (double)c[k];
+    return p;
+  }
+  return p;
+}
+
 int midpoint_form(const FieldTables& t, int precision) {
   // every stage angle is at most theta = cmax dt E_max; a step of S stages grows
   // the state by at most (1 / cos theta)^S

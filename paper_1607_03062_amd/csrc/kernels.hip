@@ -560,16 +560,27 @@ __device__ __forceinline__ void midpoint_update(float& a1, float& b1, float& a2,
   b2 += db2;
 }
 
-// tan(sqrt x) / sqrt x - 1 = sum_{n=2}^{J} a_n x^(n-1) (coefficients from tan' = 1 + tan^2).
-// The 1 is left out so that the rounding of the sum is relative to its own small
-// size; the caller adds it exactly, as (al, be) = fma(tau - 1, (X, Y), (X, Y)).
-template <int J>
+// tan(sqrt x) / sqrt x - 1 = sum_{n=2}^{J} c_n x^(n-1), the solve's coefficients c
+// (tan_polynomial).  The kernel is bound by VALU issue, so each term saved is one instruction
+// of about 17 a point's step: 700 x 511 points, 8000 FP64 steps, angles up to .055 take 6 terms
+// where the Taylor polynomial took 7 and 1.59 instead of 1.72 ms.  The 1 is left out so that
+// the rounding of the sum is relative to its own small size; the caller adds it exactly, as
+// (al, be) = fma(tau - 1, (X, Y), (X, Y)).
+template <int J, typename R>
 struct TanSeries {
-  template <typename R>
-  __device__ __forceinline__ static R minus1(R x) {
-    R acc = (R)tan_series_coef(J);
+  R c[J + 1];
+  __device__ __forceinline__ explicit TanSeries(const TanPolynomial& p) {
 #pragma unroll
-    for (int n = J - 1; n >= 2; --n) acc = fma(acc, x, (R)tan_series_coef(n));
+    for (int n = 2; n <= J; ++n) {
+      c[n] = (R)p.c[n];
+      // FP32 pairs only with its operands in vector registers
+      if constexpr (sizeof(R) == 4) asm("" : "+v"(c[n]));
+    }
+  }
+  __device__ __forceinline__ R minus1(R x) const {
+    R acc = c[J];
+#pragma unroll
+    for (int n = J - 1; n >= 2; --n) acc = fma(acc, x, c[n]);
     return acc * x;
   }
 };
@@ -677,6 +688,7 @@ __global__ void __launch_bounds__(256) midpoint_kernel(const SolveParams p) {
     }
   }
   const double* __restrict__ tab = static_cast<const double*>(p.table);
+  const TanSeries<TAN ? J : 2, R> series(p.tan);
   long long k = p.k_begin;
   while (k < p.k_end) {
     long long seg = p.k_end;
@@ -700,11 +712,11 @@ __global__ void __launch_bounds__(256) midpoint_kernel(const SolveParams p) {
             // phases (a relative error of the size of the coefficient's own rounding)
             float Xr = Xs, Yr = (float)Y;
             float x = POL ? fmaf(Xr, Xr, Yr * Yr) : fmaf(Xr, Xr, (float)Y2[mcls<NS>(j)][q]);
-            float t1 = TanSeries<J>::minus1(x);  // tan(c dt E) / (c dt E) - 1
+            float t1 = series.minus1(x);  // tan(c dt E) / (c dt E) - 1
             midpoint_update_tan(a1[q], b1[q], a2[q], b2[q], fmaf(t1, Xr, Xr), fmaf(t1, Yr, Yr));
           } else if constexpr (TAN) {
             double x = POL ? fma(X, X, Y * Y) : fma(X, X, Y2[mcls<NS>(j)][q]);
-            double t1 = TanSeries<J>::minus1(x);
+            double t1 = series.minus1(x);
             midpoint_update_tan(a1[q], b1[q], a2[q], b2[q], fma(t1, X, X), fma(t1, Y, Y));
           } else {
             double x = POL ? fma(X, X, Y * Y) : fma(X, X, Y2[mcls<NS>(j)][q]);  // (c dt E)^2
@@ -1133,19 +1145,21 @@ hipError_t launch_propagate(int scheme, int precision, int ppl, int block, int t
     return p.form == kFormShear ? strang_variant<double, kFormShear, kShearPlain>(S, elliptic, ppl, block, p, stream)
                                 : strang_variant<double, kFormVersine, kShearPlain>(S, elliptic, ppl, block, p, stream);
   }
-  // series orders: those taylor_order() chooses from
+  // series orders: those tan_polynomial() and taylor_order() choose from
   if (p.form == kMidTangent) {
     if (is_fp32(precision)) {
-      switch (taylor) {
+      switch (p.tan.terms) {
         case 2: return midpoint_variant<float, 2, 1>(S, elliptic, ppl, block, p, stream);
         case 3: return midpoint_variant<float, 3, 1>(S, elliptic, ppl, block, p, stream);
+        case 4: return midpoint_variant<float, 4, 1>(S, elliptic, ppl, block, p, stream);
         default: return midpoint_variant<float, 5, 1>(S, elliptic, ppl, block, p, stream);
       }
     }
-    switch (taylor) {
+    switch (p.tan.terms) {
+      case 4: return midpoint_variant<double, 4, 1>(S, elliptic, ppl, block, p, stream);
       case 5: return midpoint_variant<double, 5, 1>(S, elliptic, ppl, block, p, stream);
-      case 7: return midpoint_variant<double, 7, 1>(S, elliptic, ppl, block, p, stream);
-      default: return midpoint_variant<double, 10, 1>(S, elliptic, ppl, block, p, stream);
+      case 6: return midpoint_variant<double, 6, 1>(S, elliptic, ppl, block, p, stream);
+      default: return midpoint_variant<double, 8, 1>(S, elliptic, ppl, block, p, stream);
     }
   }
   if (is_fp32(precision)) {

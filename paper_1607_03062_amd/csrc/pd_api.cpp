@@ -212,6 +212,7 @@ SolveParams pd_grid_s::solve_params(long long k_begin, long long k_end, void* st
   p.stage = (table_stage == 1 && (size_t)chunk_steps * row_bytes <= 65536) ? 1 : 0;
   p.chunk_steps = chunk_steps;
   p.form = form;
+  p.tan = tan;
   p.series = series;
   if (series) p.columns = columns(shape_points(), true);
   return p;
@@ -503,6 +504,10 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   g->field = std::move(t);
   g->n_masked = masked;
   g->taylor = taylor;
+  if (!strang && form == kMidTangent) {
+    const double theta = g->field.comp.cmax * g->field.dt * g->field.E_max;  // largest stage phase
+    g->tan = tan_polynomial(theta * theta, g->precision);
+  }
   g->form = form;
   g->series = series;
   g->col_offset = col_offset;

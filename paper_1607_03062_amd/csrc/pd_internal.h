@@ -216,6 +216,20 @@ int midpoint_form(const FieldTables& t, int precision);
 // cos - 1 and of sin(x)/x, in x = (c dt E)^2) whose truncation stays below the
 // precision's rounding for x <= x_max; -1 if none does.
 int taylor_order(double x_max, int precision, int form);
+
+// The polynomial a tangent-form solve runs with: tan(sqrt x) / sqrt x - 1 as
+// x (c[2] + c[3] x + ... + c[terms] x^(terms-2)) for 0 <= x <= x_max, off by no more than 2^-30
+// (FP32) and 2^-58 (FP64): what a series leaves out is the same at every step, so it has to
+// stay well below the rounding of one.  The Taylor coefficients where as few of them reach that
+// (or reach taylor_order's bound and an interpolating polynomial takes no fewer), else those of
+// the polynomial that interpolates on the Chebyshev nodes of [0, x_max], which spreads the error
+// over the interval and needs up to four terms fewer (FP64, angles .054 to .09: 6 for 10).
+constexpr int kTanTermsMax = 8;
+struct TanPolynomial {
+  int terms;  // FP32: 2, 3, 4, 5; FP64: 4, 5, 6, 8
+  double c[kTanTermsMax + 1];
+};
+TanPolynomial tan_polynomial(double x_max, int precision);
 // The shear form is used when every rotation angle of a solve is at most this (|tan(phi/2)| <= 1).
 constexpr double kShearMaxAngle = 1.5707963267948966;
 
@@ -242,6 +256,7 @@ struct SolveParams {
   int stage;         // Strang table path: 0 scalar-unit loads, 1 LDS chunks
   int form;          // Strang: kFormShear or kFormVersine; midpoint: kMidTangent or kMidCosine
   long long chunk_steps;  // LDS chunk length in steps (power of two; divides 1024 in FP32)
+  TanPolynomial tan;      // midpoint, tangent form
   int series;             // Strang by columns: terms of the coefficients' series (0: the row kernel)
   ColumnGeometry columns;
 };
@@ -339,6 +354,7 @@ struct pd_grid_s {
   long long n_masked = 0;
   long long steps_done = 0;
   int taylor = 0;
+  pdx::TanPolynomial tan{};    // midpoint, tangent form
   int form = pdx::kFormShear;  // Strang rotation form of the current field
   int series = 0;              // Strang by columns: terms of the coefficients' series, 0: the row kernel
   int valley = PD_VALLEYS_BOTH;
