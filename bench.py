@@ -44,7 +44,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "momentum point-steps/s (FP32 vs FP64 form) at stated n(p) error; p50/p99 solve ms"
 
-# Work per point-step of the Strang propagation kernel: three plane rotations of the
+# Work per point-step of the Strang kernel by rows: three plane rotations of the
 # Bloch vector per step.  The method's own (algorithmic) work is what a rotation
 # needs; the FP32 form executes more for accuracy: each component is rounded once per
 # rotation, which costs one add per rotation beyond the three shears.
@@ -56,6 +56,14 @@ METRIC = "momentum point-steps/s (FP32 vs FP64 form) at stated n(p) error; p50/p
 FORM_NAMES = {"fp32": "FP32", "fp32fast": "fast FP32", "fp64": "FP64"}
 ALGO = {(0, "fp64"): (18, 18, 9), (0, "fp32"): (18, 21, 12), (0, "fp32fast"): (18, 17, 9),
         (1, "fp64"): (24, 24, 12), (1, "fp32"): (24, 24, 18), (1, "fp32fast"): (24, 24, 18)}
+# The kernel by columns (grids of at least 32 rows, shear form) applies the field's and the
+# point's rotation about x as one: two rotations of three FMAs a step.  PD_FP32 rounds each
+# component of the x rotation once (one add more).  A y component adds its field rotation:
+# three FMAs in FP64, the FP32 forms merge it into the point's (five FMAs and an add for two).
+COLUMN_ROWS = 32
+# (y component, precision) -> as ALGO
+COLUMNS = {(0, "fp64"): (12, 12, 6), (0, "fp32"): (12, 13, 7), (0, "fp32fast"): (12, 12, 6),
+           (1, "fp64"): (18, 18, 9), (1, "fp32"): (18, 18, 10), (1, "fp32fast"): (18, 17, 9)}
 
 
 def host_cpu_model() -> str:
@@ -84,7 +92,8 @@ def algo(info: dict, precision: str):
       (J fma), alpha, beta (2 mul), the update: FP64 3 fma per component (24 flop, 12
       instr), FP32 mul + 2 fma + add per component (24 flop, 16 instr) plus 3 conversions.
     A y component adds Y = Y0 + dy and Y^2 (2 flop; 2 instr, 3 in FP32 tangent form).
-    Every midpoint operation is part of the method's step: algorithmic = executed.  The
+    Every midpoint operation is part of the method's step: algorithmic = executed (the tangent
+    form's kernel runs with fewer than J terms where an interpolating polynomial needs fewer).  The
     points of a lane share their column, so the phase add (and its FP32 conversion) is one
     instruction per lane: the instruction count divides it by points_per_lane."""
     stages = info.get("stages", 1) or 1
@@ -106,22 +115,33 @@ def algo(info: dict, precision: str):
     return stages * flops, stages * flops, stages * instr
 
 
+def solve_work(info: dict, precision: str, ny: int):
+    """algo() for a solve of ny rows: what its kernel, by columns or by rows, does."""
+    if info["scheme"] in (0, 2) and info["rotation_form"] == 0 and ny >= COLUMN_ROWS:
+        stages = info.get("stages", 1) or 1
+        return tuple(stages * v for v in COLUMNS[(1 if info.get("elliptic") else 0, precision)])
+    return algo(info, precision)
+
+
 # MI355X vector peaks from its unit counts and clock (256 CU, 2.4 GHz): FP64
 # issues 64 lanes per clock per CU (78.6 TFLOP/s with FMA); unpacked FP32 with
 # VGPR operands issues 128 lanes per clock per CU (157.3 TFLOP/s with FMA).
 CU_CLOCKS_PER_S = 256 * 2.4e9
 LANES_PER_CLK = {"fp64": 64, "fp32": 128, "fp32fast": 128}
 PEAK_TFLOPS = {p: CU_CLOCKS_PER_S * l * 2 / 1e12 for p, l in LANES_PER_CLK.items()}
-KERNEL_SRC = os.path.join(ROOT, "paper_1607_03062_amd", "csrc", "kernels.hip")
+KERNEL_SRC = tuple(os.path.join(ROOT, "paper_1607_03062_amd", "csrc", name)
+                   for name in ("kernels.hip", "strang_columns.h", "rotations.h"))
 
 
-def kernel_hash(path: str = KERNEL_SRC) -> str:
-    """Hash of the kernel source's code: comments and whitespace removed, so that a
+def kernel_hash(paths=KERNEL_SRC) -> str:
+    """Hash of the kernel sources' code: comments and whitespace removed, so that a
     profile stays valid across edits that do not change the code."""
     import re
 
-    with open(path) as fh:
-        text = fh.read()
+    text = ""
+    for path in paths:
+        with open(path) as fh:
+            text += fh.read()
     text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
     text = re.sub(r"//[^\n]*", "", text)
     code = "".join(text.split())
@@ -302,7 +322,7 @@ def batch_object(args, pd, torch, np):
     b.close()
     for s in solvers:
         s.close()
-    algo_flop, exec_flop, instr = ALGO[(0, prec)]
+    algo_flop, exec_flop, instr = COLUMNS[(0, prec)]
     algo_flop = min(algo_flop, exec_flop)
     achieved = algo_flop * total / (dev_ms * 1e-3) / 1e12
     out = {
@@ -676,7 +696,7 @@ def main():
     t = main_form["t_total"]
     value = ps_per_solve * K / t
     kern_ms = float(np.mean(main_form["kernel_ms"]))
-    flop_a, flop_e, instr = algo(main_form["info"], args.precision)
+    flop_a, flop_e, instr = solve_work(main_form["info"], args.precision, c["grid"]["ny"])
     flop_a = min(flop_a, flop_e)  # never more than the kernel executes
     achieved = flop_a * ps_per_solve / (kern_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.precision]
@@ -733,7 +753,7 @@ def main():
     }
     if other is not None:
         okm = float(np.mean(other["kernel_ms"]))
-        fa64, fe64, i64 = algo(other["info"], "fp64")
+        fa64, fe64, i64 = solve_work(other["info"], "fp64", c["grid"]["ny"])
         fa64 = min(fa64, fe64)
         line["fp64_form"] = {
             "value": ps_per_solve * K / other["t_total"], "ms_per_step": other["t_total"] / K * 1e3,
@@ -743,7 +763,7 @@ def main():
             "valu_issue_frac": i64 * ps_per_solve / (okm * 1e-3) / (CU_CLOCKS_PER_S * LANES_PER_CLK["fp64"])}
     if fast is not None:
         fkm = float(np.mean(fast["kernel_ms"]))
-        faf, fef, fi = algo(fast["info"], alt_prec)
+        faf, fef, fi = solve_work(fast["info"], alt_prec, c["grid"]["ny"])
         faf = min(faf, fef)
         line["fp32_fast_form" if alt_prec == "fp32fast" else "fp32_once_form"] = {
             "value": ps_per_solve * K / fast["t_total"], "ms_per_step": fast["t_total"] / K * 1e3,

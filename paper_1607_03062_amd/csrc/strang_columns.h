@@ -18,10 +18,12 @@
 // and written with the grid's width between lanes; neighbouring columns are in flight
 // together on one XCD, whose L2 joins their lines.
 //
-// Measured against the row kernel on one machine, whole calls: 2048^2 x 80000 steps fast FP32
-// 54.9 -> 41.9 ms, 1500 x 2047 x 12000 FP32 8.65 -> 6.02 ms, 1024^2 x 40000 FP64 14.0 -> 9.7 ms,
-// fourth order 512^2 x 4000 FP64 4.39 -> 2.88 ms, with a y component 1024^2 x 4000 FP32 8.4 ->
-// 6.3 ms.  The FP32 forms' error against 64 bits is 0.8-0.9 of what it was: a step rounds
+// Measured against the row kernel on one machine, whole calls with the steps around it:
+// 2048^2 x 80000 steps fast FP32 51.6 -> 38.6 ms (this kernel alone 54.9 -> 41.9, before the
+// points per lane followed the launch), 1500 x 2047 x 12000 FP32 8.29 -> 5.37 ms, 1024^2 x 40000
+// FP64 13.2 -> 8.7 ms, fourth order 512^2 x 4000 FP64 4.43 -> 1.28 ms, with a y component 1024^2 x
+// 4000 FP32 8.2 -> 4.8 ms.  FP32 issues 1.56-1.63 VALU instructions of 2 per SIMD quad-cycle.
+// The FP32 forms' error against 64 bits is 0.8-0.9 of what it was: a step rounds
 // the state in two rotations instead of three.
 //
 // The FP32 forms' roundings, chosen by emulating the arithmetic on 26 solves (rms error over
