@@ -851,25 +851,34 @@ int taylor_order(double x_max, int precision, int form) {
   return -1;
 }
 
+// The series' coefficients, to the terms that double precision holds for the angles of the
+// tangent form.  A table: evaluated on each call they took 10 us of a field's set-up.
+constexpr int kTanTerms = 28;
+struct TanCoefficients {
+  double a[kTanTerms];
+  constexpr TanCoefficients() : a() {
+    for (int n = 1; n < kTanTerms; ++n) a[n] = tan_series_coef(n);
+  }
+};
+constexpr TanCoefficients kTan;
+
 TanPolynomial tan_polynomial(double x_max, int precision) {
   static const int k64[] = {4, 5, 6, 8}, k32[] = {2, 3, 4, 5};
   const bool f32 = is_fp32(precision);
   const double tol = f32 ? 0x1p-30 : 0x1p-58;
   const int* orders = f32 ? k32 : k64;
   const int count = 4;
-  // q(x) = sum_{k >= 0} b_k x^k, b_k = a_{k+2}, to the terms that double precision holds for
-  // the angles of the tangent form
-  constexpr int kTerms = 26;
-  long double b[kTerms];
-  for (int k = 0; k < kTerms; ++k) b[k] = tan_series_coef(k + 2);
+  // q(x) = sum_{k >= 0} b_k x^k
+  constexpr int kTerms = kTanTerms - 2;
+  const double* b = kTan.a + 2;
   TanPolynomial p{};
   const int taylor = taylor_order(x_max, precision, kMidTangent);
   for (int o = 0; o < count; ++o) {
     const int J = orders[o], m = J - 2;  // q by a polynomial of degree m
     p.terms = J;
     double r = 4.0 * x_max / (kPi * kPi);
-    for (int n = 2; n <= J; ++n) p.c[n] = tan_series_coef(n);
-    if (tan_series_coef(J + 1) * std::pow(x_max, J) / (1.0 - r) <= tol) return p;
+    for (int n = 2; n <= J; ++n) p.c[n] = kTan.a[n];
+    if (kTan.a[J + 1] * std::pow(x_max, J) / (1.0 - r) <= tol) return p;
     // Chebyshev nodes: |q - polynomial| <= max |q^(m+1)| / (m+1)! (x_max / 4)^(m+1) 2, and all
     // derivatives of q grow with x
     long double deriv = 0, binom = 1, power = 1;  // C(k, m+1) x_max^(k-m-1)
