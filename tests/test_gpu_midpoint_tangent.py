@@ -14,8 +14,8 @@ from .test_gpu_parity import FP32_N_ABS, FP64_N_ABS, run
 pytestmark = pytest.mark.gpu
 
 
-# largest step angle c dt E of the grid: FP32 changes at .018 and .1, FP64 at .018, .033, .101;
-# past .20 the cosine form takes over
+# largest step angle dt E of the grid; second order changes its terms near .015, .072 and .18
+# (FP32) and near .015, .03 and .092 (FP64); past .20 the cosine form takes over
 @pytest.mark.parametrize("theta", [1e-5, 0.0150, 0.0178, 0.0185, 0.030, 0.036, 0.095, 0.108, 0.19, 0.26])
 @pytest.mark.parametrize("scheme", ["midpoint", "midpoint4"])
 @pytest.mark.parametrize("ellipticity", [0.0, 0.5])
