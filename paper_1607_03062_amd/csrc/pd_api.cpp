@@ -495,11 +495,19 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   if (!g->d_partial) {
     e = device_malloc(reinterpret_cast<void**>(&g->d_partial), (size_t)density_partials(npts) * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(partials)");
-    e = device_malloc(reinterpret_cast<void**>(&g->d_rho), 2 * sizeof(double));
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(rho)");
-    if ((e = hipMemset(g->d_rho, 0, 2 * sizeof(double))) != hipSuccess) return hip_fail(e, "hipMemset(rho)");
-    if (!g->h_rho) g->h_rho = HostSlots::get();
   }
+  // each buffer by itself, so that a call after a failed one allocates what is still missing
+  if (!g->d_rho) {
+    double* rho = nullptr;
+    e = device_malloc(reinterpret_cast<void**>(&rho), 2 * sizeof(double));
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc(rho)");
+    if ((e = hipMemset(rho, 0, 2 * sizeof(double))) != hipSuccess) {
+      release(rho);
+      return hip_fail(e, "hipMemset(rho)");
+    }
+    g->d_rho = rho;
+  }
+  if (!g->h_rho) g->h_rho = HostSlots::get();
   g->spare_field = std::move(g->field);
   g->field = std::move(t);
   g->n_masked = masked;

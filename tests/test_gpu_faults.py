@@ -52,6 +52,27 @@ def test_allocation_and_launch_faults_of_a_solve(gpu, faults, prec, scheme):
     assert np.array_equal(n, ref[0]) and rho == ref[1]
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+def test_a_field_set_after_a_failed_allocation_has_every_buffer(gpu, faults, k):
+    """Whichever of a new handle's allocations fails (tables, n, partials, rho), the next
+    pd_set_field makes it: a second fault armed at that call's first allocation strikes.  A
+    buffer taken for allocated would be a kernel's null pointer."""
+    grid, N = wl.grid(48, 2.0), 900
+    ref = clean(gpu, grid, "fp64", N)
+    s = gpu.Solver.for_grid(grid, "fp64")
+    for fault in ("alloc@%d" % k, "alloc@1"):
+        faults(fault)
+        with pytest.raises(gpu.PDError) as e:
+            s.set_field(FIELD, N)
+        assert e.value.status == _lib.PD_ERR_NOMEM, fault
+    s.set_field(FIELD, N)
+    s.propagate(-1)
+    n = np.empty(s.nx * s.ny)
+    rho = s.density(n_out=n)
+    s.close()
+    assert np.array_equal(n, ref[0]) and rho == ref[1]
+
+
 def test_launch_faults_of_batch_epochs_and_runs(gpu, faults):
     specs = [(wl.grid(64, 2.0), "fp32", 900), (wl.grid(96, 2.0), "fp64", 1300), (wl.grid(1024, 3.0), "fp32", 700),
              (wl.grid(80, 2.0), "fp32", 1100)]
