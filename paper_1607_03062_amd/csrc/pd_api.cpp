@@ -484,9 +484,6 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(field table)");
     g->table_capacity = table_need;
   }
-  g->table_bytes = rows.size();
-  e = hipMemcpy(g->d_table, rows.data(), rows.size(), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpy(field table)");
   long long npts = g->grid.points();
   if (!g->d_n) {
     e = device_malloc(reinterpret_cast<void**>(&g->d_n), (size_t)npts * sizeof(double));
@@ -501,13 +498,19 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
     double* rho = nullptr;
     e = device_malloc(reinterpret_cast<void**>(&rho), 2 * sizeof(double));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(rho)");
-    if ((e = hipMemset(rho, 0, 2 * sizeof(double))) != hipSuccess) {
+    // a blocking copy, complete when it returns: the next density may come on a stream that
+    // waits for nothing enqueued here, where a fill might still be under way
+    const double zero[2] = {};
+    if ((e = hipMemcpy(rho, zero, sizeof zero, hipMemcpyHostToDevice)) != hipSuccess) {
       release(rho);
-      return hip_fail(e, "hipMemset(rho)");
+      return hip_fail(e, "hipMemcpy(rho)");
     }
     g->d_rho = rho;
   }
   if (!g->h_rho) g->h_rho = HostSlots::get();
+  g->table_bytes = rows.size();
+  e = hipMemcpy(g->d_table, rows.data(), rows.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return hip_fail(e, "hipMemcpy(field table)");
   g->spare_field = std::move(g->field);
   g->field = std::move(t);
   g->n_masked = masked;

@@ -47,3 +47,19 @@ def test_density_and_snapshot(gpu, nx, ny, scheme, precision):
     st.synchronize()
     assert np.array_equal(only_n.cpu().numpy(), end[1])
     s.close()
+
+
+def test_first_density_of_new_handles_on_a_stream_that_waits_for_nothing(gpu):
+    """What a first pd_set_field clears is cleared when it returns: the first density of each
+    of many new handles, on a stream without any order to the default one."""
+    import torch
+
+    st = torch.cuda.Stream()
+    g, f = wl.grid(40, 1.5), wl.sin2(0.2, 0.6, 2)
+    got = []
+    for _ in range(40):
+        s = gpu.Solver.for_grid(g, "fp64").set_field(f, 64)
+        got.append(s.propagate(-1, stream=st).density(stream=st))
+        got.append(s.density(stream=st))
+        s.close()
+    assert got[0] > 0 and got.count(got[0]) == len(got)
