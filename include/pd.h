@@ -248,7 +248,8 @@ pd_status pd_density(pd_grid g, double* n_out, int n_out_on_device, double* rho_
    nothing.  Grids of at most 2^28 points (16384 x 16384); larger ones return
    PD_ERR_INVALID before any device work.  Every call on a device shares that
    device's scratch, so calls that overlap on one device (on different streams or
-   threads) race; calls ordered on one stream do not. */
+   threads) race and may return a wrong rho; calls ordered on one stream do not, and
+   calls after the overlapping ones are not affected. */
 pd_status pd_density_static(pd_grid g, double* n_out, int n_out_on_device, double* rho_out, void* stream);
 
 /* Time-resolved occupation after the steps done so far (0 <= steps_done <= N,

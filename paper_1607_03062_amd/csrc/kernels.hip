@@ -951,7 +951,9 @@ struct StoredDensity {
 // One pass over the points: a point's value from `value`, kept in n_store and copied to
 // n_copy (each may be null), its tile's sum into partial[tile].  `done` (null: a second
 // launch sums the partials): the blocks count themselves there, and the last one sums the
-// partials, writes rho and clears the count for the next pass.
+// partials and writes rho.  The count goes round modulo the number of blocks: every pass
+// that counts there has as many (one handle's grid), so it is 0 again after any number of
+// them, also where two overlapped and mixed their counts.
 //
 // What bounds it: for small grids its own launch and the wait for it, so one launch does
 // what took four (values, tile sums, their sum, the copy of n) and the copy of rho to the
@@ -980,7 +982,9 @@ __global__ void __launch_bounds__(kRedThreads) density_pass(const Value value, l
   __shared__ bool last;
   if (threadIdx.x == 0) {
     __hip_atomic_store(partial + tile, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x;
+    __threadfence();  // the sum before the count, and the count before the others' sums
+    last = atomicInc(done, gridDim.x - 1u) == gridDim.x - 1u;
+    __threadfence();
   }
   __syncthreads();
   if (!last) return;
@@ -990,7 +994,6 @@ __global__ void __launch_bounds__(kRedThreads) density_pass(const Value value, l
   __syncthreads();  // the first sum's shared values have been read
   r = block_sum(r);
   if (threadIdx.x == 0) {
-    __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *rho = scale * r;
     if (rho_host) *rho_host = scale * r;
   }
@@ -1215,11 +1218,12 @@ hipError_t launch_snapshot(int scheme, int precision, int elliptic, const SolveP
 
 // ---------------------------------------------------------------------------
 // Static scratch of the no-allocation density (pd_density_static): the tile partials
-// of one reduction, then its sum, then its blocks' count.  Each device holds its own copy until the process
-// ends; every call on a device shares it.
+// of one reduction, then its sum.  Each device holds its own copy until the process
+// ends; every call on a device shares it, so nothing in it outlasts a call: every partial is
+// written before it is read, and the blocks are counted in the handle's own memory.
 
 static_assert(kRedTile * kStaticPartials == kStaticMaxPoints, "static scratch sized for the reduction's tiles");
-static __device__ __align__(256) double scratch[kStaticPartials + 2];
+static __device__ __align__(256) double scratch[kStaticPartials + 1];
 
 namespace {
 constexpr int kMaxDevices = 64;

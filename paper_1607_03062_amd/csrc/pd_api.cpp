@@ -699,12 +699,18 @@ pd_status finish_density(pd_grid g, const double* d_rho, double* n_out, int n_ou
   return ok();
 }
 
-DensityOut density_out(pd_grid g, double* partial, double* rho, double* n_out, int n_out_on_device) {
+// The outputs of a density call.  The slot is written only for a call that reads it, and
+// holds NaN until then, so that no earlier call's rho can pass for this one's.
+DensityOut density_out(pd_grid g, double* partial, double* rho, double* n_out, int n_out_on_device,
+                       const double* rho_out) {
   DensityOut o{};
   o.partial = partial;
   o.rho = rho;
-  o.done = reinterpret_cast<unsigned*>(rho + 1);
-  o.rho_host = g->h_rho;
+  o.done = reinterpret_cast<unsigned*>(g->d_rho + 1);
+  if (rho_out && g->h_rho) {
+    *static_cast<volatile double*>(g->h_rho) = std::nan("");
+    o.rho_host = g->h_rho;
+  }
   o.n_copy = n_out_on_device ? n_out : nullptr;
   o.scale = g->density_scale();
   return o;
@@ -717,7 +723,7 @@ pd_status density_call(pd_grid g, double* partial, double* rho, double* n_out, i
   const long long npts = g->grid.points();
   hipError_t e = hipSuccess;
   if (rho_out) {
-    e = launch_density(g->d_n, npts, density_out(g, partial, rho, n_out, n_out_on_device), s);
+    e = launch_density(g->d_n, npts, density_out(g, partial, rho, n_out, n_out_on_device, rho_out), s);
     if (e != hipSuccess) return hip_fail(e, "density launch");
   } else if (n_out && n_out_on_device) {
     e = hipMemcpyAsync(n_out, g->d_n, (size_t)npts * sizeof(double), hipMemcpyDeviceToDevice, s);
@@ -755,10 +761,10 @@ pd_status pd_density_static(pd_grid g, double* n_out, int n_out_on_device, doubl
   double* sc = nullptr;
   hipError_t e = static_scratch(g->device, &sc);
   if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-  // partials in sc[0 .. tiles), the sum in sc[kStaticPartials], then the count of the
-  // pass's blocks, 0 between passes.  The handle's completion event exists once a
-  // propagation was enqueued outside capture; otherwise a later pd_set_field waits for
-  // the device (creating an event here could allocate).
+  // partials in sc[0 .. tiles), the sum in sc[kStaticPartials]; the blocks' count is the
+  // handle's.  The handle's completion event exists once a propagation was enqueued
+  // outside capture; otherwise a later pd_set_field waits for the device (creating an
+  // event here could allocate).
   return density_call(g, sc, sc + kStaticPartials, n_out, n_out_on_device, rho_out, static_cast<hipStream_t>(stream),
                       false);
 }
@@ -790,7 +796,7 @@ pd_status pd_snapshot(pd_grid g, double* n_out, int n_out_on_device, double* rho
       rotation_coefficients(-half, g->form, &q.undo_a, &q.undo_s);
     }
     hipError_t e = launch_snapshot(g->scheme, g->precision, g->field.elliptic ? 1 : 0, p, q,
-                                   density_out(g, g->d_partial, g->d_rho, n_out, n_out_on_device), s);
+                                   density_out(g, g->d_partial, g->d_rho, n_out, n_out_on_device, rho_out), s);
     if (e != hipSuccess) return hip_fail(e, "snapshot launch");
     return finish_density(g, g->d_rho, n_out, n_out_on_device, rho_out, s, true);
   }

@@ -301,8 +301,8 @@ struct DensityJob {
 hipError_t launch_propagate(int scheme, int precision, int points_per_lane, int block_threads, int taylor,
                             int elliptic, const SolveParams& p, hipStream_t stream);
 // What a density pass writes beside n: its tile sums, rho on the device and (if not null)
-// in page-locked host memory, a copy of n (if not null).  `done`: the blocks' count, 0
-// between passes.
+// in page-locked host memory, a copy of n (if not null).  `done`: where the blocks of this
+// handle's passes count themselves, and no other's (density_pass).
 struct DensityOut {
   double* partial;
   unsigned* done;
@@ -319,7 +319,7 @@ hipError_t launch_density(const double* n, long long npts, const DensityOut& o, 
 constexpr long long kStaticMaxPoints = 1LL << 28;
 constexpr long long kStaticPartials = kStaticMaxPoints / 2048;
 // Device address of the static scratch on `device` (kStaticPartials partials, then
-// one sum and the pass's block count), looked up on the first call for that device.
+// one sum), looked up on the first call for that device.
 hipError_t static_scratch(int device, double** out);
 // The persistent kernels of a batch: tiles of the row kernel, and waves' units of the
 // column kernels.  Each has its own work items and its own counter.
@@ -367,7 +367,7 @@ struct pd_grid_s {
   size_t col_offset = 0, row_offset = 0;
   double* d_n = nullptr;
   double* d_partial = nullptr;
-  double* d_rho = nullptr;    // the sum, then the count of the density pass's blocks
+  double* d_rho = nullptr;    // the sum, then the count of the density passes' blocks
   double* h_rho = nullptr;    // where the device leaves rho for the host (HostSlots)
   void* d_state_own = nullptr;
   void* d_state_bound = nullptr;

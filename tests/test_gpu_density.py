@@ -63,3 +63,34 @@ def test_first_density_of_new_handles_on_a_stream_that_waits_for_nothing(gpu):
         got.append(s.density(stream=st))
         s.close()
     assert got[0] > 0 and got.count(got[0]) == len(got)
+
+
+def test_overlapping_static_densities_leave_later_calls_alone(gpu):
+    """Two threads call pd_density_static on handles of 4 and of 10 tiles at the same time, each
+    on its own stream: those calls share the device's scratch and may be wrong, what comes
+    after them may not."""
+    import threading
+
+    import torch
+
+    f, made = wl.sin2(0.3, 0.6, 2), []
+    for n in (90, 140):
+        s = gpu.Solver.for_grid(wl.grid(n, 1.5), "fp64").set_field(f, 150)
+        st = torch.cuda.Stream()
+        s.propagate(-1, stream=st)
+        made.append((s, st, s.density(stream=st)))
+
+    def call(s, st):
+        for _ in range(300):
+            s.density_static(stream=st)
+
+    threads = [threading.Thread(target=call, args=(s, st)) for s, st, _ in made]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for s, st, rho in made + made[::-1]:
+        assert s.density_static(stream=st) == rho and s.density(stream=st) == rho
+        assert s.snapshot(stream=st) == rho
+    for s, _, _ in made:
+        s.close()
