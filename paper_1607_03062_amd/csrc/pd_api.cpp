@@ -670,15 +670,30 @@ pd_status pd_propagate(pd_grid g, long long max_steps, void* stream) {
 
 namespace {
 
-// The end of a density call: the copies the pass did not make, the wait where something goes
-// to the host, and rho from the slot the pass wrote (or, without one, copied from d_rho).
-// The handle's work up to here is then complete, or noted if the call does not wait.
-pd_status finish_density(pd_grid g, const double* d_rho, double* n_out, int n_out_on_device, double* rho_out,
-                         hipStream_t s, bool may_create_event) {
+// Whether kernels of the handle's device may store to p: memory of that device.  What else a
+// copy reaches (another device's memory without peer access, managed memory, host memory) is
+// left to a copy.
+bool stored_by_kernel(pd_grid g, const double* p) {
+  if (reinterpret_cast<uintptr_t>(p) % sizeof(double) != 0) return false;
+  hipPointerAttribute_t a{};
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == g->device && !a.isManaged;
+}
+
+// The end of a density call: the copy of n unless the pass made it (n_copied), the wait where
+// something goes to the host, and rho from the slot the pass wrote (or, without one, copied
+// from d_rho).  The handle's work up to here is then complete, or noted if the call does not
+// wait.
+pd_status finish_density(pd_grid g, const double* d_rho, double* n_out, int n_out_on_device, bool n_copied,
+                         double* rho_out, hipStream_t s, bool may_create_event) {
   hipError_t e;
   double rho = 0.0;
-  if (n_out && !n_out_on_device) {
-    e = hipMemcpyAsync(n_out, g->d_n, (size_t)g->grid.points() * sizeof(double), hipMemcpyDeviceToHost, s);
+  if (n_out && !n_copied) {
+    e = hipMemcpyAsync(n_out, g->d_n, (size_t)g->grid.points() * sizeof(double),
+                       n_out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s);
     if (e != hipSuccess) return hip_fail(e, "copy of n(p)");
   }
   if (rho_out && !g->h_rho) {
@@ -711,7 +726,7 @@ DensityOut density_out(pd_grid g, double* partial, double* rho, double* n_out, i
     *static_cast<volatile double*>(g->h_rho) = std::nan("");
     o.rho_host = g->h_rho;
   }
-  o.n_copy = n_out_on_device ? n_out : nullptr;
+  o.n_copy = n_out && n_out_on_device && stored_by_kernel(g, n_out) ? n_out : nullptr;
   o.scale = g->density_scale();
   return o;
 }
@@ -720,16 +735,14 @@ DensityOut density_out(pd_grid g, double* partial, double* rho, double* n_out, i
 // scratch.  Without a rho to return it is a copy of n.
 pd_status density_call(pd_grid g, double* partial, double* rho, double* n_out, int n_out_on_device, double* rho_out,
                        hipStream_t s, bool may_create_event) {
-  const long long npts = g->grid.points();
-  hipError_t e = hipSuccess;
+  bool n_copied = false;
   if (rho_out) {
-    e = launch_density(g->d_n, npts, density_out(g, partial, rho, n_out, n_out_on_device, rho_out), s);
+    const DensityOut o = density_out(g, partial, rho, n_out, n_out_on_device, rho_out);
+    const hipError_t e = launch_density(g->d_n, g->grid.points(), o, s);
     if (e != hipSuccess) return hip_fail(e, "density launch");
-  } else if (n_out && n_out_on_device) {
-    e = hipMemcpyAsync(n_out, g->d_n, (size_t)npts * sizeof(double), hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "copy of n(p)");
+    n_copied = o.n_copy != nullptr;
   }
-  return finish_density(g, rho, n_out, n_out_on_device, rho_out, s, may_create_event);
+  return finish_density(g, rho, n_out, n_out_on_device, n_copied, rho_out, s, may_create_event);
 }
 
 }  // namespace
@@ -795,10 +808,10 @@ pd_status pd_snapshot(pd_grid g, double* n_out, int n_out_on_device, double* rho
       double half = g->vsign() * 0.5 * g->field.dt * (g->field.comp.c[0] * g->field.Ay_mid[(size_t)(k * S)]);
       rotation_coefficients(-half, g->form, &q.undo_a, &q.undo_s);
     }
-    hipError_t e = launch_snapshot(g->scheme, g->precision, g->field.elliptic ? 1 : 0, p, q,
-                                   density_out(g, g->d_partial, g->d_rho, n_out, n_out_on_device, rho_out), s);
+    const DensityOut o = density_out(g, g->d_partial, g->d_rho, n_out, n_out_on_device, rho_out);
+    hipError_t e = launch_snapshot(g->scheme, g->precision, g->field.elliptic ? 1 : 0, p, q, o, s);
     if (e != hipSuccess) return hip_fail(e, "snapshot launch");
-    return finish_density(g, g->d_rho, n_out, n_out_on_device, rho_out, s, true);
+    return finish_density(g, g->d_rho, n_out, n_out_on_device, o.n_copy != nullptr, rho_out, s, true);
   }
   return density_call(g, g->d_partial, g->d_rho, n_out, n_out_on_device, rho_out, s, true);
 }

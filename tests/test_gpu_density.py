@@ -94,3 +94,36 @@ def test_overlapping_static_densities_leave_later_calls_alone(gpu):
         assert s.snapshot(stream=st) == rho
     for s, _, _ in made:
         s.close()
+
+
+def test_n_to_memory_that_only_a_copy_reaches(gpu):
+    """n_out_on_device = 1 with an address that is no memory of the handle's device (here
+    page-locked host memory), and one that is not a multiple of 8: what the copy engine
+    reaches, the call serves, from pd_density, pd_density_static and pd_snapshot."""
+    import ctypes
+
+    import torch
+
+    from paper_1607_03062_amd import _lib
+
+    m = 60 * 50
+    s = gpu.Solver.for_grid({"nx": 60, "ny": 50, "px": (-1.3, 1.2), "py": (-1.1, 1.4)}, "fp64")
+    s.set_field(wl.sin2(0.3, 0.6, 2), 300)
+    pinned = torch.zeros(m, dtype=torch.float64, pin_memory=True)
+    raw = torch.zeros(8 * m + 8, dtype=torch.uint8, device="cuda")
+    lib, st = _lib.load(), torch.cuda.Stream()
+    for name in ("pd_snapshot", "pd_density", "pd_density_static"):
+        if name != "pd_density_static":
+            s.propagate(150, stream=st)
+        want = np.empty(m)
+        rho_want = (s.snapshot if name == "pd_snapshot" else s.density)(n_out=want, stream=st)
+        for address in (pinned.data_ptr(), raw.data_ptr() + 4):
+            rho = ctypes.c_double()
+            assert getattr(lib, name)(s.handle, address, 1, ctypes.byref(rho), _lib.stream_handle(st)) == 0
+            st.synchronize()
+            got = pinned.numpy() if address == pinned.data_ptr() else raw[4:4 + 8 * m].cpu().numpy().view(np.float64)
+            assert rho.value == rho_want and np.array_equal(got, want), name
+            pinned.zero_()
+            raw.zero_()
+            torch.cuda.synchronize()
+    s.close()
