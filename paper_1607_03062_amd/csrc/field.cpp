@@ -446,7 +446,9 @@ bool sample_field(const pd_field& f, long long n_steps, const Composition& comp,
   t.Ay_min = std::fmin(t.Ay_in, t.Ay_out);
   t.Ay_max = std::fmax(t.Ay_in, t.Ay_out);
   const bool x_ok = value_range(t.A_mid, &t.A_min, &t.A_max), y_ok = value_range(t.Ay_mid, &t.Ay_min, &t.Ay_max);
-  if (!x_ok || !y_ok) {
+  // The end values by themselves: fmin and fmax pass over a NaN, and a pulse whose rise has
+  // no finite integral need not have a sample there.
+  if (!x_ok || !y_ok || !finite(t.A_in) || !finite(t.A_out) || !finite(t.Ay_in) || !finite(t.Ay_out)) {
     *err = "field has a non-finite value";
     return false;
   }

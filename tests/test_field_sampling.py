@@ -36,3 +36,14 @@ def test_large_phases():
     f = dict(PULSE, phi=3e6, ellipticity=0.0)
     Ax = _lib.sample_field_xy(f, 500, "strang")[0]
     assert np.max(np.abs(Ax - oracle.field_table(f, 500, "strang")[0])) <= 8 * 3e6 * 2.0 ** -52
+
+
+@pytest.mark.parametrize("omega_rise", [np.inf, 1e308])
+@pytest.mark.parametrize("omega_fall", [0.11, np.inf])
+@pytest.mark.parametrize("N", [1, 7, 300])
+def test_a_pulse_without_a_finite_rise_is_refused(omega_rise, omega_fall, N):
+    """Also where no sample lies in a part whose integral is not finite."""
+    for ellipticity in (0.0, 0.6):
+        with pytest.raises(_lib.PDError) as e:
+            _lib.sample_field_xy(dict(PULSE, omega_rise=omega_rise, omega_fall=omega_fall, ellipticity=ellipticity), N)
+        assert e.value.status == _lib.PD_ERR_INVALID
