@@ -17,6 +17,10 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 
+// Phase below which the sines at the ends of an interval are not subtracted: their
+// difference, divided by the frequency, has lost some 1 / phase of its digits.
+constexpr double kShortPhase = 0.5;
+
 // 2 sin^2(x/2) = 1 - cos x without cancellation at small x.
 double versine(double x) {
   double s = std::sin(0.5 * x);
@@ -53,15 +57,19 @@ struct LaserPulse {
   double E0, w, phi, Wr, Wf, D;
   double tr() const { return kPi / (2.0 * Wr); }
   double ta() const { return D - kPi / (2.0 * Wf); }
-  // int_a^b cos(w t + q) dt
-  double carrier(double q, double a, double b) const { return (std::sin(w * b + q) - std::sin(w * a + q)) / w; }
-  // int_a^b cos(2 W (t - c)) cos(w t + q) dt
+  // int_a^b cos(w t + q) dt: the difference of the sines, or over less than kShortPhase the
+  // interval times the cosine at its middle times sin(h) / h, h half the phase it covers,
+  // which loses nothing to a small w.
+  static double carrier(double w, double q, double a, double b) {
+    const double h = 0.5 * (w * (b - a));
+    if (std::fabs(2.0 * h) < kShortPhase)
+      return (b - a) * (h != 0.0 ? std::sin(h) / h : 1.0) * std::cos(w * (0.5 * (a + b)) + q);
+    return (std::sin(w * b + q) - std::sin(w * a + q)) / w;
+  }
+  double carrier(double q, double a, double b) const { return carrier(w, q, a, b); }
+  // int_a^b cos(2 W (t - c)) cos(w t + q) dt, the side bands w + 2 W and w - 2 W
   double beat(double q, double W, double c, double a, double b) const {
-    double w1 = w + 2.0 * W, q1 = q - 2.0 * W * c;
-    double w2 = w - 2.0 * W, q2 = q + 2.0 * W * c;
-    double i1 = (std::sin(w1 * b + q1) - std::sin(w1 * a + q1)) / w1;
-    double i2 = (w2 != 0.0) ? (std::sin(w2 * b + q2) - std::sin(w2 * a + q2)) / w2 : (b - a) * std::cos(q2);
-    return 0.5 * (i1 + i2);
+    return 0.5 * (carrier(w + 2.0 * W, q - 2.0 * W * c, a, b) + carrier(w - 2.0 * W, q + 2.0 * W * c, a, b));
   }
   // -E0 int_0^t env(s) cos(w s + q) ds
   double A_phase(double q, double t) const {
@@ -115,6 +123,7 @@ void eval_A(const pd_field& f, double t, double* ax, double* ay) {
 struct SineSum {
   double end = 0, c0 = 0, lin = 0;
   bool squared = false;
+  bool slow = false;  // a sine covers less than kShortPhase: c0 cancels it
   int n = 0;
   double amp[3] = {}, freq[3] = {}, phase[3] = {};
   void add(double a, double w, double q) {
@@ -242,6 +251,7 @@ int pieces_of(const pd_field& f, bool y, SineSum out[3]) {
           else
             p.lin = sign * a * std::cos(q + 2.0 * W * c);
         }
+        for (int i = 0; i < p.n; ++i) p.slow = p.slow || std::fabs(p.freq[i] * (p.end - t)) < kShortPhase;
         p.pass_through(t, value);
         t = p.end;
         value = (y ? f.ellipticity * lp.A_phase(q, t) : lp.A_phase(q, t));
@@ -251,7 +261,9 @@ int pieces_of(const pd_field& f, bool y, SineSum out[3]) {
   }
 }
 
-// Samples [k0, k1) of every stage of one component into `out` (stage stride S).
+// Samples [k0, k1) of every stage of one component into `out` (stage stride S).  One by one
+// where a sine of a piece is slow (its amplitude over a small frequency and c0 cancel) or a
+// phase is past sin_lane's range.
 void sample_component(const pd_field& f, bool y, double t_i, double dt, const Composition& comp, long long k0,
                       long long k1, double* out) {
   SineSum p[3];
@@ -261,6 +273,7 @@ void sample_component(const pd_field& f, bool y, double t_i, double dt, const Co
   for (int i = 0; i < m; ++i)
     for (int q = 0; q < p[i].n; ++q)
       in_range = in_range && std::fabs(p[i].freq[q]) * p[i].end + std::fabs(p[i].phase[q]) < kSinLaneMax;
+  const auto side_by_side = [&](const SineSum& f) { return in_range && !f.slow; };
   for (int j = 0; j < S; ++j) {
     const auto time = [&](long long k) { return t_i + ((double)k + comp.sigma[j]) * dt; };
     long long k = k0;
@@ -274,7 +287,7 @@ void sample_component(const pd_field& f, bool y, double t_i, double dt, const Co
       }
       for (; k < e; k += kSpan) {
         const int n = (int)std::min<long long>(kSpan, e - k);
-        if (in_range) {
+        if (side_by_side(p[i])) {
           span(p[i], t_i, (double)k, comp.sigma[j], dt, n, out + (size_t)k * S + j, S);
         } else {
           double ax, ay;

@@ -47,3 +47,45 @@ def test_a_pulse_without_a_finite_rise_is_refused(omega_rise, omega_fall, N):
         with pytest.raises(_lib.PDError) as e:
             _lib.sample_field_xy(dict(PULSE, omega_rise=omega_rise, omega_fall=omega_fall, ellipticity=ellipticity), N)
         assert e.value.status == _lib.PD_ERR_INVALID
+
+
+def _integral(f, phase, t):
+    """-E0 int_0^t env(s) cos(omega s + phase) ds at the increasing times t: Gauss-Legendre
+    rules of 16 nodes between the times, the corners of the envelope and 400 even steps, summed
+    in extended precision."""
+    L = np.longdouble
+    pi = L("3.14159265358979323846264338")
+    W = [L(f["omega_rise"]), L(f["omega_fall"])]
+    corners = [pi / (2 * W[0]), L(f["duration"]) - pi / (2 * W[1])]
+    x, w = np.polynomial.legendre.leggauss(16)
+    edges = np.sort(np.concatenate([corners, t.astype(L), np.linspace(0, f["duration"], 401).astype(L)]))
+    a, h = edges[:-1, None], np.diff(edges)[:, None] / 2
+    s = a + h * (1 + x.astype(L))
+    env = np.where(s < corners[0], np.sin(W[0] * s) ** 2, np.where(s > corners[1], np.cos(W[1] * (s - corners[1])) ** 2, 1))
+    parts = (h * w.astype(L) * env * np.cos(L(f["omega"]) * s + L(phase))).sum(axis=1)
+    total = np.concatenate([[L(0)], np.cumsum(parts)])
+    return -L(f["E0"]) * total[np.searchsorted(edges, t.astype(L), side="right") - 1]
+
+
+# a side band at a frequency near zero, in the rise and in the fall, and a carrier of far less
+# than a period: what divides by the small frequency has to lose nothing to it
+@pytest.mark.parametrize("detuning", [5e-17, 1e-12, 1e-9, 1e-6, 1e-4, 1e-2, 0.2])
+@pytest.mark.parametrize("part", ["omega_rise", "omega_fall", "omega"])
+@pytest.mark.parametrize("N", [3, 300])
+def test_slow_parts_of_a_pulse(detuning, part, N):
+    f = {"kind": "pulse", "E0": 0.8, "omega": 0.6, "phi": 0.4, "omega_rise": 0.07, "omega_fall": 0.11,
+         "duration": 60.0, "ellipticity": 1.0}
+    if part == "omega":
+        f["omega"] = 0.6 * detuning
+    else:
+        f[part] = 0.1 * 3 * (1 + detuning)  # 0.1 * 3 is not 0.3: off the resonance by a rounding
+    got = _lib.sample_field_xy(f, N)
+    t = (np.arange(N) + 0.5) * (f["duration"] / N)
+    # a rounding of each term's phase (up to 80 here), once per end of each of three parts
+    w, span = f["omega"], np.pi / 2 / 0.07
+    size = min(1 / w, 60.0) + 0.25 / (w + 0.14) + span / 4
+    tol = 3 * 2.0 ** -52 * (1 + 60 * (w + 0.62)) * f["E0"] * size
+    ends = np.array([f["duration"]])
+    for samples, end, phase in ((got[0], got[2][3], 0.4), (got[1], got[2][5], 0.4 - 0.5 * np.pi)):
+        assert np.max(np.abs(samples - _integral(f, phase, t))) <= tol
+        assert abs(end - _integral(f, phase, ends)[0]) <= tol
