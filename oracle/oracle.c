@@ -166,16 +166,23 @@ static double sin2_Ey(double E0y, double w, int cycles, double t) {
    (the fall factor is taken so that the envelope goes from 1 to 0 across the
    fall window; the equation as printed does not vanish at t_f).  A is the
    closed-form antiderivative, piece by piece, continuous at the joins. */
+static double cos_int(double w, double p, double a, double b) {
+  /* int_a^b cos(w t + p) dt; a small phase between a and b by the product form of the
+     difference of sines, 2 sin((B - A)/2) cos((A + B)/2), which does not cancel. */
+  double d = w * (b - a);
+  if (d == 0.0) return (b - a) * cos(p + w * a);
+  if (fabs(d) < 0.5) return 2.0 * sin(0.5 * d) * cos(0.5 * w * (a + b) + p) / w;
+  return (sin(w * b + p) - sin(w * a + p)) / w;
+}
+
 static double pulse_env_int(double w, double phi, double W, double shift, int fall, double a, double b) {
   /* int_a^b env(t) cos(w t + phi) dt with env = sin^2(W (t - shift)) (rise) or cos^2(W (t - shift)) (fall).
      sin^2 u = (1 - cos 2u)/2, cos^2 u = (1 + cos 2u)/2;
      cos(2W(t-s)) cos(w t + phi) = [cos((w+2W)t + phi - 2Ws) + cos((w-2W)t + phi + 2Ws)]/2. */
   double sgn = fall ? 1.0 : -1.0;
-  double base = (sin(w * b + phi) - sin(w * a + phi)) / w;
-  double w1 = w + 2.0 * W, p1 = phi - 2.0 * W * shift;
-  double w2 = w - 2.0 * W, p2 = phi + 2.0 * W * shift;
-  double t1 = (sin(w1 * b + p1) - sin(w1 * a + p1)) / w1;
-  double t2 = (fabs(w2) > 0.0) ? (sin(w2 * b + p2) - sin(w2 * a + p2)) / w2 : (b - a) * cos(p2);
+  double base = cos_int(w, phi, a, b);
+  double t1 = cos_int(w + 2.0 * W, phi - 2.0 * W * shift, a, b);
+  double t2 = cos_int(w - 2.0 * W, phi + 2.0 * W * shift, a, b);
   return 0.5 * base + sgn * 0.25 * (t1 + t2);
 }
 
@@ -191,7 +198,7 @@ static double pulse_A_phase(const oracle_problem* f, double phi, double t) {
   I += pulse_env_int(w, phi, f->omega_rise, 0.0, 0, 0.0, b);
   if (t > tr) {
     double b2 = t < t_fall0 ? t : t_fall0;
-    if (b2 > tr) I += (sin(w * b2 + phi) - sin(w * tr + phi)) / w;
+    if (b2 > tr) I += cos_int(w, phi, tr, b2);
     if (t > t_fall0) I += pulse_env_int(w, phi, f->omega_fall, t_fall0, 1, t_fall0, t);
   }
   return -f->E0 * I;

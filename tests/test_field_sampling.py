@@ -79,13 +79,14 @@ def test_slow_parts_of_a_pulse(detuning, part, N):
         f["omega"] = 0.6 * detuning
     else:
         f[part] = 0.1 * 3 * (1 + detuning)  # 0.1 * 3 is not 0.3: off the resonance by a rounding
-    got = _lib.sample_field_xy(f, N)
+    got, of_oracle = _lib.sample_field_xy(f, N), (oracle.field_table(f, N)[0], oracle.field_table_y(f, N)[0])
     t = (np.arange(N) + 0.5) * (f["duration"] / N)
     # a rounding of each term's phase (up to 80 here), once per end of each of three parts
     w, span = f["omega"], np.pi / 2 / 0.07
     size = min(1 / w, 60.0) + 0.25 / (w + 0.14) + span / 4
     tol = 3 * 2.0 ** -52 * (1 + 60 * (w + 0.62)) * f["E0"] * size
     ends = np.array([f["duration"]])
-    for samples, end, phase in ((got[0], got[2][3], 0.4), (got[1], got[2][5], 0.4 - 0.5 * np.pi)):
-        assert np.max(np.abs(samples - _integral(f, phase, t))) <= tol
+    for samples, other, end, phase in zip(got, of_oracle, (got[2][3], got[2][5]), (0.4, 0.4 - 0.5 * np.pi)):
+        want = _integral(f, phase, t)
+        assert np.max(np.abs(samples - want)) <= tol and np.max(np.abs(other - want)) <= tol
         assert abs(end - _integral(f, phase, ends)[0]) <= tol
