@@ -58,12 +58,13 @@ ALGO = {(0, "fp64"): (18, 18, 9), (0, "fp32"): (18, 21, 12), (0, "fp32fast"): (1
         (1, "fp64"): (24, 24, 12), (1, "fp32"): (24, 24, 18), (1, "fp32fast"): (24, 24, 18)}
 # The kernel by columns (grids of at least 32 rows, shear form) applies the field's and the
 # point's rotation about x as one: two rotations of three FMAs a step.  PD_FP32 rounds each
-# component of the x rotation once (one add more).  A y component adds its field rotation:
-# three FMAs in FP64, the FP32 forms merge it into the point's (five FMAs and an add for two).
+# component once per rotation (one add more each).  A y component adds its field rotation:
+# three FMAs, an add more in PD_FP32; the fast form merges it into the point's (five FMAs and
+# an add for two).
 COLUMN_ROWS = 32
 # (y component, precision) -> as ALGO
-COLUMNS = {(0, "fp64"): (12, 12, 6), (0, "fp32"): (12, 13, 7), (0, "fp32fast"): (12, 12, 6),
-           (1, "fp64"): (18, 18, 9), (1, "fp32"): (18, 18, 10), (1, "fp32fast"): (18, 17, 9)}
+COLUMNS = {(0, "fp64"): (12, 12, 6), (0, "fp32"): (12, 14, 8), (0, "fp32fast"): (12, 12, 6),
+           (1, "fp64"): (18, 18, 9), (1, "fp32"): (18, 21, 12), (1, "fp32fast"): (18, 17, 9)}
 
 
 def host_cpu_model() -> str:

@@ -60,13 +60,9 @@ typedef enum {
   PD_FP32 = 1,     /* precision form: FP32 state and rotations; FP64 time, field table,
                       rotation angles, projection and density sum; the state is
                       renormalised every 1024 absolute steps (the exact step is unitary,
-                      Sec. III).  Strang: the rotations about x round each state component
-                      once, those about y are plain shears (one component rounded twice)
-                      whose orientation alternates from one stage to the next; grids of
-                      fewer than 32 rows, and steps too large for one rotation about x
-                      (pd_info.rotation_form), round each component once in every rotation */
+                      Sec. III); every rotation rounds each state component once */
   PD_FP32_FAST = 2 /* as PD_FP32, but every Strang rotation is plain shears, of alternating
-                      orientation: 6 instructions for a point's step instead of 7.  On the
+                      orientation: 6 instructions for a point's step instead of 8.  On the
                       2048^2 benchmark solve every point is within 1e-5 of FP64 in both
                       forms; over long solves on wide grids the worst points of this one are
                       further off than PD_FP32's, so it is not held to PD_FP32's bound (the

@@ -20,18 +20,21 @@
 //
 // Measured against the row kernel on one machine, whole calls with the steps around it:
 // 2048^2 x 80000 steps fast FP32 51.6 -> 38.6 ms (this kernel alone 54.9 -> 41.9, before the
-// points per lane followed the launch), 1500 x 2047 x 12000 FP32 8.29 -> 5.37 ms, 1024^2 x 40000
+// points per lane followed the launch), 1500 x 2047 x 12000 FP32 8.29 -> 5.99 ms, 1024^2 x 40000
 // FP64 13.2 -> 8.7 ms, fourth order 512^2 x 4000 FP64 4.43 -> 1.28 ms, with a y component 1024^2 x
-// 4000 FP32 8.2 -> 4.8 ms.  FP32 issues 1.56-1.63 VALU instructions of 2 per SIMD quad-cycle.
-// The FP32 forms' error against 64 bits is 0.8-0.9 of what it was: a step rounds
-// the state in two rotations instead of three.
+// 4000 FP32 8.2 -> 5.6 ms.  Fast FP32 issues 1.56-1.63 VALU instructions of 2 per SIMD
+// quad-cycle.
 //
-// The FP32 forms' roundings, chosen by emulating the arithmetic on 26 solves (rms error over
-// that of the row kernel's form, geometric mean and worst): PD_FP32 rounds each component
-// once in the rotations about x only (7 instructions, 0.80 and 1.27; once in all: 8, 0.76
-// and 1.40; plain alternating shears: 6, 0.94 and 1.51).  PD_FP32_FAST turns both rotations
-// over together from stage to stage (0.83 and 1.14 of its own row form; other patterns of
-// orientations 0.79-0.91 and up to 1.81).
+// The FP32 forms' roundings.  PD_FP32 rounds each component once in every rotation (8
+// instructions for a point's step; the row kernel's three rotations 12).  PD_FP32_FAST: plain
+// shears, both rotations turned over together from stage to stage (6; 9).  Two rotations a
+// step round less than three: over 225 solves (64 full grids of 256^2 to 2048^2 points and 5000
+// to 80000 steps, the 2048^2 x 80000 solve, 160 drawn ones with fourth order and a y component
+// among them) the rms error against FP64 is 0.80 of the row kernel's in PD_FP32 (worst solve
+// 0.96) and 0.86 in PD_FP32_FAST (1.05), the worst point's 0.79 (1.28) and 0.84 (1.57), the
+// worst of all points 1.45e-5 after 1.80e-5 and 3.14e-5 after 3.15e-5.  Plain shears about y
+// alone in PD_FP32 (7 instructions) had a worst point of 2.75e-5, and 2.0 times the row
+// kernel's in one solve.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -171,7 +174,7 @@ __device__ __forceinline__ constexpr bool orientation_x(int odd) {
 }
 template <int SH>
 __device__ __forceinline__ constexpr bool orientation_y(int odd) {
-  return SH != kShearPlain && odd != 0;
+  return SH == kShearAlt && odd != 0;
 }
 
 // The Bloch vectors of a lane's points, PPL consecutive rows of one column, and the
@@ -197,17 +200,17 @@ struct ColumnLanes {
     for (int q = 0; q < PPL; ++q) {
       rotate_oriented<SH == kShearOnce>(y[q], z[q], ex.t, ex.s, orientation_x<SH>(o));
       if constexpr (kOrientedY && !closing) {
-        rotate_oriented<false>(z[q], x[q], aY[c][h][q], sY[c][h][q], orientation_y<SH>(o));
+        rotate_oriented<SH == kShearOnce>(z[q], x[q], aY[c][h][q], sY[c][h][q], orientation_y<SH>(o));
       } else {
         const R ya = closing ? ha[q] : aY[c][h][q], ys = closing ? hs[q] : sY[c][h][q];
-        if constexpr (POL && sizeof(R) == 4) {
+        if constexpr (POL && SH == kShearAlt) {
           if (orientation_y<SH>(o))
             rotate_two_shear_vu(z[q], x[q], ya, ys, ef.t, ef.s);
           else
             rotate_two_shear(z[q], x[q], ya, ys, ef.t, ef.s);
         } else {
-          rot<kFormShear, sizeof(R) == 4 ? kShearAlt : kShearPlain>(z[q], x[q], ya, ys, orientation_y<SH>(o));
-          if constexpr (POL) rot<kFormShear, kShearPlain>(z[q], x[q], ef.t, ef.s);
+          rot<kFormShear, SH>(z[q], x[q], ya, ys, orientation_y<SH>(o));
+          if constexpr (POL) rot<kFormShear, SH>(z[q], x[q], ef.t, ef.s);
         }
       }
     }

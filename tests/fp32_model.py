@@ -10,13 +10,15 @@ can be predicted on the CPU before the kernels run:
   * coefficients t = tan(theta/2), s = sin(theta) computed in FP64 and rounded to FP32;
     the per-point ones take four FP32 values in turn (step k uses value k mod 4) whose
     mean is within 1/8 ulp of the FP64 value;
+  * kernel "columns" (grids of at least 32 rows, half angles up to pi/4): the two rotations
+    about x as one, by 2 dt P_x, whose coefficients are rounded after a shift of 3/8, -1/8,
+    1/8, -3/8 ulp in turn; kernel "rows": the field part, then the point's part;
   * arrangement "once" (PD_FP32): every rotation as three shears, each state component
     rounded once per rotation (u1 = u - t v; v' = v + s u1; u' = u - t (v + v'));
     arrangement "fast" (PD_FP32_FAST): plain shears whose orientation alternates from
-    step to step (u-v-u, then v-u-v), the step's two rotations about x (field part,
-    then the point's part) as five shears, the middle two merged into one with the
-    summed coefficient; a fused multiply-add is one rounding, emulated as an exact FP64
-    product and sum rounded to FP32;
+    step to step (u-v-u, then v-u-v), by rows with the step's two rotations about x
+    as five shears, the middle two merged into one with the summed coefficient; a fused
+    multiply-add is one rounding, emulated as an exact FP64 product and sum rounded to FP32;
   * the state renormalised in FP64 every 1024 steps; the initial state and the
     projection n = (1 + r.P_out/|P_out|) / 2 (Sec. II, Eqs. (1), (3)) in FP64.
 
@@ -41,11 +43,21 @@ def _coefficients(theta):
 
 
 def _phases(c):
-    """PHASES FP32 values per FP64 coefficient whose mean is within 1/8 ulp of it."""
-    hi = c.astype(F32)
-    ulp = np.spacing(np.abs(hi)).astype(np.float64)
-    m = np.rint(PHASES * (c - hi.astype(np.float64)) / np.where(ulp > 0, ulp, 1.0))
-    return np.stack([(hi + np.where(j < np.abs(m), np.sign(m), 0.0) * ulp).astype(F32) for j in range(PHASES)])
+    """PHASES FP32 values per FP64 coefficient whose mean is within 1/8 ulp of it: its upper
+    FP32 neighbour (of the magnitude) in the first so many phases in bit-reversed order."""
+    a = np.abs(c)
+    lo = a.astype(F32)
+    lo = np.where(lo.astype(np.float64) > a, np.nextafter(lo, F32(0)), lo)
+    hi = np.nextafter(lo, F32(np.inf))
+    up = np.floor(PHASES * (a - lo.astype(np.float64)) / (hi.astype(np.float64) - lo.astype(np.float64)) + 0.5)
+    return np.stack([(np.where(rank < up, hi, lo) * np.sign(c)).astype(F32) for rank in (0, 2, 1, 3)])
+
+
+def _shifted(c, k):
+    """The FP32 value of a column's coefficient at step k: rounded after a shift of 3/8, -1/8,
+    1/8, -3/8 of 2^-23 of its power of two."""
+    power = np.ldexp(np.sign(c), np.frexp(c)[1] - 1)
+    return (c + power * ((0.375, -0.125, 0.125, -0.375)[k % PHASES] * 2.0 ** -23)).astype(F32)
 
 
 def _rotate(u, v, t, s, arithmetic):
@@ -90,16 +102,20 @@ def _shears(u, v, coefs, odd, arithmetic):
     return u, v
 
 
-def solve_grid(field, grid, n_steps, arithmetic=F32, arrangement="once"):
+def solve_grid(field, grid, n_steps, arithmetic=F32, arrangement="once", kernel=None):
     """n(p) on the grid (row-major, y rows) after n_steps second-order Strang steps in the
-    given arithmetic and arrangement of the roundings; NaN where |p + A(t_i)| or
-    |p + A(t_f)| is 0 (masked points)."""
+    given arithmetic and arrangement of the roundings, by the kernel the library runs such a
+    grid with, or the one named; NaN where |p + A(t_i)| or |p + A(t_f)| is 0 (masked points)."""
     if arrangement not in ("once", "fast"):
         raise ValueError("arrangement must be 'once' or 'fast'")
+    if kernel is None:
+        kernel = "columns" if grid["ny"] >= 32 else "rows"
     A, a_in, a_out, dt = oracle.field_table(field, n_steps)
     px = np.array([oracle.grid_p(grid["px"][0], grid["px"][1], grid["nx"], i) for i in range(grid["nx"])])
     py = np.array([oracle.grid_p(grid["py"][0], grid["py"][1], grid["ny"], j) for j in range(grid["ny"])])
     PX, PY = (a.ravel() for a in np.meshgrid(px, py))
+    if kernel == "columns" and dt * np.hypot(np.abs(px).max() + np.abs(A).max(), np.abs(py).max()) > 0.25 * np.pi:
+        raise ValueError("step too large for the kernel by columns")
     with np.errstate(invalid="ignore", divide="ignore"):
         e_in = np.hypot(PX + a_in, PY)
         x = (-(PX + a_in) / e_in).astype(arithmetic)  # v_in: r = -P_in / |P_in|
@@ -127,6 +143,16 @@ def solve_grid(field, grid, n_steps, arithmetic=F32, arrangement="once"):
             x, y, z = ((c / nr).astype(F32) for c in (X, Y, Z))
         h = k % PHASES
         yt, ys = (th, sh) if k == n_steps - 1 else (ty[h], sy[h])
+        if kernel == "columns":
+            t, s = (c if arithmetic is np.float64 else _shifted(c, k) for c in _coefficients(2.0 * dt * (px + A[k])))
+            t, s = np.tile(t, py.size), np.tile(s, py.size)
+            if arrangement == "fast":
+                y, z = _shears(y, z, [(t, s)], k % 2 == 1, arithmetic)
+                z, x = _shears(z, x, [(yt, ys)], k % 2 == 1, arithmetic)
+            else:
+                y, z = _rotate(y, z, t, s, arithmetic)
+                z, x = _rotate(z, x, yt, ys, arithmetic)
+            continue
         if arrangement == "fast":
             y, z = _shears(y, z, [(tf[k], sf[k]), (tx[h], sx[h])], k % 2 == 1, arithmetic)
             z, x = _shears(z, x, [(yt, ys)], k % 2 == 1, arithmetic)

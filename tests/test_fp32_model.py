@@ -42,3 +42,21 @@ def test_coefficient_phases_average_to_the_fp64_value():
     assert ph.dtype == np.float32 and ph.shape == (4, c.size)
     assert np.all(np.abs(ph.astype(np.float64).mean(axis=0) - c) <= ulp / 8 + 1e-300)
     assert np.all(np.abs(ph.astype(np.float64) - c) <= ulp)
+
+
+@pytest.mark.parametrize("kernel", ["columns", "rows"])
+@pytest.mark.parametrize("arrangement", ["once", "fast"])
+def test_both_kernels_in_fp64_are_the_oracle(kernel, arrangement):
+    n_o = oracle.solve_grid(FIELD, GRID, 1500)[0]
+    n = fp32_model.solve_grid(FIELD, GRID, 1500, np.float64, arrangement, kernel)
+    assert fp32_model.error_stats(n, n_o)[0] <= 1e-12
+
+
+def test_one_rotation_about_x_is_not_further_off_than_two():
+    """Each component rounded once per rotation, of which the kernel by columns has two a step
+    instead of three."""
+    for N in (4000, 16000):
+        n_o = oracle.solve_grid(FIELD, GRID, N)[0]
+        columns, rows = (fp32_model.error_stats(fp32_model.solve_grid(FIELD, GRID, N, kernel=k), n_o)
+                         for k in ("columns", "rows"))
+        assert columns[0] <= rows[0] and columns[1] <= rows[1], (N, columns, rows)
