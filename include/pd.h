@@ -148,10 +148,14 @@ typedef struct {
   int scheme;               /* pd_scheme */
   int points_per_lane;      /* launch shape in use: as set, or chosen by the library (then up to 8) */
   int block_threads;
-  int table_stage;          /* 1 = LDS chunks, 2 = scalar-unit reads */
+  int table_stage;          /* 1 = LDS chunks, 2 = scalar-unit reads: as set, whether or not the
+                               solve's kernel reads its table so (pd_set_launch) */
   int chunk_steps;
   int rotation_form;        /* Strang: 0 = three shears per rotation (every rotation angle of the
-                               solve <= pi/2), 1 = versine form (h = cos - 1, s = sin).
+                               solve <= pi/2), 1 = versine form (h = cos - 1, s = sin).  Form 0 on
+                               at least 32 rows, with dt |p + A| (0.66 of it in the fourth order)
+                               at most pi/4, runs by columns: the field's and the point's rotation
+                               about x as one.
                                Midpoint: 0 = tangent form (the step divided by cos(dt E), one
                                series; chosen when the state's growth over 1024 steps stays
                                below 2^32), 1 = cosine form (cos - 1 and sin(x)/x) */
@@ -316,15 +320,15 @@ pd_status pd_save_state(pd_grid g, void* host, size_t bytes, long long* steps_do
 pd_status pd_load_state(pd_grid g, const void* host, size_t bytes, long long steps_done, void* stream);
 
 /* Override the launch shape of the propagation kernel: points_per_lane in
-   {1, 2, 4}; block_threads in {64, 128, 256}; table_stage 1 = the per-step
+   {1, 2, 4}, or the value pd_info reports for this handle; block_threads in {64, 128, 256}; table_stage 1 = the per-step
    field rows are staged through LDS in time chunks (read from VGPRs), 2 = read
    directly by the scalar unit (SGPR operands); chunk_steps = LDS chunk length,
    a power of two in [64, 4096] (at most 1024 in the FP32 form, whose
    renormalisation period it must divide); a solve whose chunk of rows would
    exceed 64 KiB of LDS (long rows: fourth order, y component) reads them with the
-   scalar unit instead.  A Strang solve of at least 32 rows keeps coefficients of its own
-   in the LDS whatever the stage and the chunk; its points per lane, if never set, follow
-   the grid's size.  0 keeps the current value.  Results do not depend on the
+   scalar unit instead.  A Strang solve by columns (pd_info.rotation_form) keeps coefficients
+   of its own in the LDS whatever the stage and the chunk; its points per lane, if never
+   set, follow the grid's size.  0 keeps the current value.  Results do not depend on the
    launch shape (bit for bit). */
 pd_status pd_set_launch(pd_grid g, int points_per_lane, int block_threads, int table_stage, int chunk_steps);
 
@@ -336,9 +340,9 @@ void pd_destroy_grid(pd_grid g);
 /* Choose the launch shape of g by timing candidates on the first
    min(trial_steps, N) steps of g's own solve on `stream`: points_per_lane
    {1, 2, 4} x block_threads {64, 256} x (scalar-unit rows, LDS chunks of 256 or
-   1024 steps for Strang), or, for a Strang solve of at least 32 rows,
-   points_per_lane {1, 2, 4, 8} x block_threads {64, 256}.  The fastest is applied as by pd_set_launch; the solve
-   is left rewound (steps_done = 0).  With use_cache != 0 and the environment
+   1024 steps for Strang), or, for a Strang solve by columns, points_per_lane
+   {1, 2, 4, 8} x block_threads {64, 256}.  The fastest is applied as by pd_set_launch
+   (8 for the solves by columns only: another runs with 4); the solve is left rewound (steps_done = 0).  With use_cache != 0 and the environment
    variable PD_AUTOTUNE_CACHE naming a file, a shape stored there for the same
    (GPU architecture, precision, scheme, rotation form, floor(log2 points)) is
    applied without timing, and a newly timed one is appended. */

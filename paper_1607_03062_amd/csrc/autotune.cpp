@@ -69,7 +69,8 @@ bool cache_lookup(const std::string& key, Shape* out) {
   return found;
 }
 
-// pd_set_launch, and the column kernels' eight points per lane, which it does not offer.
+// pd_set_launch, and the column kernels' eight points per lane, which it takes only where the
+// solve runs with them already.
 pd_status apply(pd_grid g, const Shape& s) {
   const bool eight = s.ppl == 8 && g->series;
   const pd_status r = pd_set_launch(g, eight ? 0 : s.ppl, s.block, s.stage, s.chunk);

@@ -612,7 +612,8 @@ pd_status pd_load_state(pd_grid g, const void* host, size_t bytes, long long ste
 
 pd_status pd_set_launch(pd_grid g, int points_per_lane, int block_threads, int table_stage, int chunk_steps) {
   if (!g) return fail(PD_ERR_INVALID, "null handle");
-  if (points_per_lane != 0 && points_per_lane != 1 && points_per_lane != 2 && points_per_lane != 4)
+  if (points_per_lane != 0 && points_per_lane != 1 && points_per_lane != 2 && points_per_lane != 4 &&
+      points_per_lane != g->shape_points())
     return fail(PD_ERR_INVALID, "points_per_lane must be 1, 2 or 4");
   if (block_threads != 0 && block_threads != 64 && block_threads != 128 && block_threads != 256)
     return fail(PD_ERR_INVALID, "block_threads must be 64, 128 or 256");

@@ -393,10 +393,12 @@ struct pd_grid_s {
   double density_scale() const;
   // Launch parameters of steps [k_begin, k_end); `state` is the chunk state buffer (may be null).
   pdx::SolveParams solve_params(long long k_begin, long long k_end, void* state) const;
-  // Points per lane the solve runs with.
+  // Points per lane the solve runs with (the autotuner's 8 of a solve by columns is not kept
+  // for one that runs another kernel, which has none for it).
   int shape_points() const {
-    if (points_chosen || !field_set) return points_per_lane;
-    if (!series && pdx::base_scheme(scheme) != PD_SCHEME_MIDPOINT) return points_per_lane;
+    const int set = series ? points_per_lane : std::min(points_per_lane, 4);
+    if (points_chosen || !field_set) return set;
+    if (!series && pdx::base_scheme(scheme) != PD_SCHEME_MIDPOINT) return set;
     return pdx::auto_points_per_lane(grid, scheme, precision, field.comp.stages, field.elliptic ? 1 : 0);
   }
   // alone: the solve's own launch; else a member of a batch's persistent launch

@@ -142,3 +142,29 @@ def test_fp32_roundings_are_the_models(gpu, precision, arrangement, ny):
     model = fp32_model.solve_grid(f, g, N, arrangement=arrangement)
     ok = np.isfinite(model)
     assert np.mean(np.abs(n - model)[ok] > 1e-12) <= 0.01
+
+
+def test_eight_points_per_lane_as_reported(gpu):
+    """The points per lane that a handle reports can be set on it; eight stay with the solves by
+    columns: not for a smaller grid, nor for a field that takes the handle to the other kernel."""
+    g, f, N = _grid(1019, 1021), wl.sin2(0.3, 0.6, 3), 700
+    big, wide = gpu.Solver.for_grid(g, "fp64").set_field(f, N), wl.constant(0.05, 40.0)
+    shape = big.info()["points_per_lane"]
+    assert shape == 8
+    rho = big.solve()
+    assert big.set_launch(shape).rewind().solve() == rho and big.info()["points_per_lane"] == 8
+
+    small = gpu.Solver.for_grid(_grid(20, 40), "fp64").set_field(f, N)
+    with pytest.raises(gpu.PDError):
+        small.set_launch(8)
+    small.close()
+
+    steps = math.ceil(40.0 * big.check_field(wide, 400)["E_max"])  # dt |p + A| up to 1
+    big.set_field(wide, steps)
+    assert big.info()["points_per_lane"] == 4
+    other = gpu.Solver.for_grid(g, "fp64").set_field(wide, steps)
+    assert big.solve() == other.solve()
+    with pytest.raises(gpu.PDError):
+        big.set_launch(8)
+    big.close()
+    other.close()
