@@ -35,6 +35,7 @@ import argparse
 import ctypes
 import hashlib
 import json
+import math
 import os
 import sys
 import time
@@ -62,6 +63,7 @@ ALGO = {(0, "fp64"): (18, 18, 9), (0, "fp32"): (18, 21, 12), (0, "fp32fast"): (1
 # three FMAs, an add more in PD_FP32; the fast form merges it into the point's (five FMAs and
 # an add for two).
 COLUMN_ROWS = 32
+FOURTH_ORDER_STAGE = 4 / (4 - 4 ** (1 / 3)) - 1  # its longest stage, of a step
 # (y component, precision) -> as ALGO
 COLUMNS = {(0, "fp64"): (12, 12, 6), (0, "fp32"): (12, 14, 8), (0, "fp32fast"): (12, 12, 6),
            (1, "fp64"): (18, 18, 9), (1, "fp32"): (18, 21, 12), (1, "fp32fast"): (18, 17, 9)}
@@ -117,9 +119,11 @@ def algo(info: dict, precision: str):
 
 
 def solve_work(info: dict, precision: str, ny: int):
-    """algo() for a solve of ny rows: what its kernel, by columns or by rows, does."""
-    if info["scheme"] in (0, 2) and info["rotation_form"] == 0 and ny >= COLUMN_ROWS:
-        stages = info.get("stages", 1) or 1
+    """algo() for a solve of ny rows: what its kernel, by columns (shears, at least 32 rows, half
+    angles up to pi/4) or by rows, does."""
+    stages = info.get("stages", 1) or 1
+    half = info["dt"] * info["E_max"] * (FOURTH_ORDER_STAGE if stages == 5 else 1.0)
+    if info["scheme"] in (0, 2) and info["rotation_form"] == 0 and ny >= COLUMN_ROWS and half <= 0.25 * math.pi:
         return tuple(stages * v for v in COLUMNS[(1 if info.get("elliptic") else 0, precision)])
     return algo(info, precision)
 
