@@ -101,43 +101,46 @@ pd_status hip_error(hipError_t e, const char* what) {
 namespace {
 constexpr int kSlotsPerPage = 256;
 struct SlotPage {
-  double* base;
-  std::vector<int> free;
+  double* base = nullptr;
+  int n_free = 0;
+  int free[kSlotsPerPage];  // slots not handed out: free[0 .. n_free)
+  SlotPage* next = nullptr;
 };
 std::mutex g_slots_mu;
-std::vector<SlotPage> g_slot_pages;
+SlotPage* g_slot_pages = nullptr;  // not an object with a destructor: handles may outlive the others at exit
 }  // namespace
 
 double* HostSlots::get() {
   std::lock_guard<std::mutex> lock(g_slots_mu);
-  for (SlotPage& p : g_slot_pages)
-    if (!p.free.empty()) {
-      const int i = p.free.back();
-      p.free.pop_back();
-      return p.base + i;
-    }
+  for (SlotPage* p = g_slot_pages; p; p = p->next)
+    if (p->n_free) return p->base + p->free[--p->n_free];
+  SlotPage* p = new (std::nothrow) SlotPage;
+  if (!p) return nullptr;
   void* mem = nullptr;
   if (hipHostMalloc(&mem, kSlotsPerPage * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
     (void)hipGetLastError();
+    delete p;
     return nullptr;
   }
-  SlotPage p{static_cast<double*>(mem), {}};
-  p.free.reserve(kSlotsPerPage);
-  for (int i = kSlotsPerPage - 1; i > 0; --i) p.free.push_back(i);
-  g_slot_pages.push_back(std::move(p));
-  return static_cast<double*>(mem);
+  p->base = static_cast<double*>(mem);
+  for (int i = kSlotsPerPage - 1; i > 0; --i) p->free[p->n_free++] = i;
+  p->next = g_slot_pages;
+  g_slot_pages = p;
+  return p->base;
 }
 
 void HostSlots::put(double* slot) {
   if (!slot) return;
   std::lock_guard<std::mutex> lock(g_slots_mu);
-  for (size_t k = 0; k < g_slot_pages.size(); ++k) {
-    SlotPage& p = g_slot_pages[k];
-    if (slot < p.base || slot >= p.base + kSlotsPerPage) continue;
-    p.free.push_back((int)(slot - p.base));
-    if ((int)p.free.size() == kSlotsPerPage) {
-      (void)hipHostFree(p.base);
-      g_slot_pages.erase(g_slot_pages.begin() + (long)k);
+  for (SlotPage** at = &g_slot_pages; *at; at = &(*at)->next) {
+    SlotPage* p = *at;
+    if (slot < p->base || slot >= p->base + kSlotsPerPage) continue;
+    p->free[p->n_free++] = (int)(slot - p->base);
+    // the last page stays, for the next handle of a program that uses one after another
+    if (p->n_free == kSlotsPerPage && (p != g_slot_pages || p->next)) {
+      *at = p->next;
+      (void)hipHostFree(p->base);
+      delete p;
     }
     return;
   }

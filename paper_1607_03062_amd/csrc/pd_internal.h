@@ -415,9 +415,9 @@ struct pd_grid_s {
 
 namespace pdx {
 // Doubles of page-locked host memory that kernels write and the host reads, handed out from
-// pages that the process's handles share (a page-locked allocation of its own for each would
-// cost more than a small solve); a page is freed when its last slot is given back.  Safe from
-// several threads.  get: null if no page can be allocated.
+// pages of 2 KiB that the process's handles share (a page-locked allocation of its own for each
+// would cost more than a small solve); a page is freed when its last slot is given back, the
+// last page excepted.  Safe from several threads.  get: null if no page can be allocated.
 struct HostSlots {
   static double* get();
   static void put(double* slot);

@@ -1,0 +1,196 @@
+// The library's host code (pd_api.cpp, field.cpp) against a model of the HIP runtime and of the
+// launches: device memory is host memory, a copy is a memcpy, a launch records what it was given
+// (test_host_model.py builds and runs it).  For what the host side does with allocations, copies
+// and pointers, where the device would show a mistake as a fault or not at all.  Prints one line
+// per failed check and "host model ok"; the exit status is the number of failures.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <set>
+#include <vector>
+
+#include "pd_internal.h"
+
+using namespace pdx;
+
+static int failures = 0;
+static void expect(bool cond, const char* what) {
+  if (!cond) {
+    std::printf("FAIL %s: %s\n", what, pd_last_error());
+    ++failures;
+  }
+}
+
+// ---- the runtime ----------------------------------------------------------------------
+
+static std::set<void*> device_blocks;
+static int host_pages = 0, host_allocs = 0, fills = 0, copies_of_n = 0;
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = std::malloc(n ? n : 1);
+  device_blocks.insert(*p);
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  device_blocks.erase(p);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int) {
+  *p = std::malloc(n);
+  ++host_pages;
+  ++host_allocs;
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  std::free(p);
+  --host_pages;
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(d, s, n);
+  if (n > sizeof(double)) ++copies_of_n;
+  return hipSuccess;
+}
+hipError_t hipMemset(void* d, int v, size_t n) {  // may return before it is done
+  std::memset(d, v, n);
+  ++fills;
+  return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  std::memset(a, 0, sizeof *a);
+  if (!device_blocks.count(const_cast<void*>(p))) return hipErrorInvalidValue;
+  a->type = hipMemoryTypeDevice;
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "model"; }
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  *e = reinterpret_cast<hipEvent_t>(std::malloc(1));
+  return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) {
+  std::free(reinterpret_cast<void*>(e));
+  return hipSuccess;
+}
+}
+
+// ---- the launches ---------------------------------------------------------------------
+
+static DensityOut last_density;
+namespace pdx {
+hipError_t launch_propagate(int, int, int, int, int, int, const SolveParams& p, hipStream_t) {
+  for (long long i = 0; i < p.npts; ++i) p.n_out[i] = 1.0;
+  return hipSuccess;
+}
+static hipError_t density(const DensityOut& o, long long npts) {
+  last_density = o;
+  if (!o.partial || !o.rho) return hipErrorInvalidValue;
+  *o.rho = o.scale * (double)npts;
+  if (o.rho_host) *o.rho_host = *o.rho;
+  for (long long i = 0; o.n_copy && i < npts; ++i) o.n_copy[i] = 1.0;
+  return hipSuccess;
+}
+hipError_t launch_snapshot(int, int, int, const SolveParams& p, const SnapshotParams&, const DensityOut& o,
+                           hipStream_t) {
+  for (long long i = 0; i < p.npts; ++i) p.n_out[i] = 1.0;
+  return density(o, p.npts);
+}
+hipError_t launch_density(const double*, long long npts, const DensityOut& o, hipStream_t) { return density(o, npts); }
+hipError_t static_scratch(int, double** out) {
+  static std::vector<double> scratch(kStaticPartials + 1);
+  *out = scratch.data();
+  return hipSuccess;
+}
+long long density_partials(long long npts) { return (npts + 2047) / 2048; }
+size_t state_values_per_point(int scheme) { return base_scheme(scheme) == PD_SCHEME_MIDPOINT ? 4 : 3; }
+}  // namespace pdx
+
+// ---- checks ---------------------------------------------------------------------------
+
+static pd_field field() {
+  pd_field f;
+  std::memset(&f, 0, sizeof f);
+  f.kind = PD_FIELD_SIN2;
+  f.E0 = 0.2;
+  f.omega = 0.6;
+  f.cycles = 3;
+  return f;
+}
+
+static pd_grid grid(int n = 40) {
+  pd_grid g = nullptr;
+  expect(pd_create_grid(n, n, -2.0, 2.0, -2.0, 2.0, PD_FP64, PD_SCHEME_STRANG, &g) == PD_OK, "grid");
+  return g;
+}
+
+// What any of a new handle's allocations left missing, the next pd_set_field makes.
+static void check_failed_allocations() {
+  const pd_field f = field();
+  for (int k = 1; k <= 4; ++k) {
+    pd_grid g = grid();
+    char spec[16];
+    std::snprintf(spec, sizeof spec, "alloc@%d", k);
+    double rho = 0.0;
+    pd_set_fault(spec);
+    expect(pd_set_field(g, &f, 500) == PD_ERR_NOMEM, spec);
+    pd_set_fault(nullptr);
+    expect(pd_set_field(g, &f, 500) == PD_OK, "field after a failed allocation");
+    expect(g->d_table && g->d_n && g->d_partial && g->d_rho, "every buffer is there");
+    if (g->d_rho) {
+      expect(pd_propagate(g, -1, nullptr) == PD_OK && pd_density(g, nullptr, 0, &rho, nullptr) == PD_OK, "solve");
+      expect(rho > 0.0, "rho");
+    }
+    pd_destroy_grid(g);
+  }
+  expect(fills == 0, "what is cleared is cleared by a copy, which waits");
+}
+
+// Handles one after another use one page; the pages of many are given back but for one.
+static void check_slots() {
+  const pd_field f = field();
+  const int before = host_allocs;
+  for (int i = 0; i < 20; ++i) {
+    pd_grid g = grid();
+    expect(pd_set_field(g, &f, 100) == PD_OK, "field");
+    pd_destroy_grid(g);
+  }
+  expect(host_allocs <= before + 1, "one page for handles one after another");
+  std::vector<pd_grid> many;
+  std::set<double*> slots;
+  for (int i = 0; i < 600; ++i) {
+    many.push_back(grid(2));
+    expect(pd_set_field(many.back(), &f, 100) == PD_OK, "field");
+    slots.insert(many.back()->h_rho);
+  }
+  expect(slots.size() == 600 && !slots.count(nullptr), "a slot of its own for each");
+  expect(host_pages == 3, "three pages for 600 handles");
+  for (pd_grid g : many) pd_destroy_grid(g);
+  expect(host_pages == 1, "one page stays");
+}
+
+int main() {
+  check_failed_allocations();
+  check_slots();
+  expect(device_blocks.empty(), "all device memory is given back");
+  if (!failures) std::printf("host model ok\n");
+  return failures;
+}
