@@ -296,6 +296,24 @@ size_t table_footprint(pd_grid g, long long n_steps) {
   return table;
 }
 
+// What a handle keeps of its host buffers for the next field: up to 1 MiB each, 131072 FP64
+// samples.  Below, a new allocation's page faults cost as much as filling it (20000 steps: 40
+// pages); above, the solve is longer by far.
+constexpr size_t kKeptBytes = 1 << 20;
+struct TrimHostBuffers {
+  pd_grid g;
+  template <typename T>
+  static void trim(std::vector<T>& v) {
+    if (v.capacity() * sizeof(T) > kKeptBytes) std::vector<T>().swap(v);
+  }
+  ~TrimHostBuffers() {
+    if (!g) return;
+    trim(g->upload);
+    trim(g->spare_field.A_mid);
+    trim(g->spare_field.Ay_mid);
+  }
+};
+
 void fill_info(pd_grid g, const FieldTables& t, long long masked, long long steps_done, pd_info* out) {
   std::memset(out, 0, sizeof *out);
   out->n_points = g->grid.points();
@@ -449,6 +467,7 @@ pd_status pd_set_valley(pd_grid g, int valley) {
 
 pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   TraceCall trace("pd_set_field");
+  const TrimHostBuffers trim{g};
   FieldTables t;
   if (g) t = std::move(g->spare_field);
   long long masked = 0;

@@ -348,7 +348,8 @@ struct pd_grid_s {
 
   bool field_set = false;
   pdx::FieldTables field;
-  // host buffers of the last field but one and of the upload, kept for the next field
+  // host buffers of the last field but one and of the upload, kept for the next field where
+  // they are small (kKeptBytes)
   pdx::FieldTables spare_field;
   std::vector<unsigned char> upload;
   long long n_masked = 0;

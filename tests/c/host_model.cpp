@@ -187,9 +187,61 @@ static void check_slots() {
   expect(host_pages == 1, "one page stays");
 }
 
+// The buffers a handle keeps beside its field's samples do not grow with the step count.
+static void check_kept_memory() {
+  pd_field f = field();
+  f.ellipticity = 0.5;
+  pd_grid g = grid();
+  for (long long n : {200000LL, 300000LL, 500LL, 400000LL, 400000LL}) {
+    expect(pd_set_field(g, &f, n) == PD_OK, "field");
+    expect(g->field.A_mid.size() == (size_t)n && g->field.Ay_mid.size() == (size_t)n, "the field's samples");
+    expect(g->upload.capacity() + 8 * (g->spare_field.A_mid.capacity() + g->spare_field.Ay_mid.capacity()) <= 3 << 20,
+           "at most 3 MiB beside them");
+  }
+  pd_set_fault("alloc@1");  // the table of a longer field: the buffers of a call that fails, too
+  expect(pd_set_field(g, &f, 900000) == PD_ERR_NOMEM, "injected fault");
+  pd_set_fault(nullptr);
+  expect(g->upload.capacity() <= 1 << 20, "the upload of a failed call");
+  pd_destroy_grid(g);
+}
+
+// n(p) for a device address: stored by the pass to memory of the device, copied to any other.
+static void check_copy_of_n() {
+  const pd_field f = field();
+  pd_grid g = grid();
+  const size_t m = 1600;
+  void* device = nullptr;
+  hipMalloc(&device, m * sizeof(double) + 8);
+  std::vector<double> elsewhere(m);
+  expect(pd_set_field(g, &f, 500) == PD_OK && pd_propagate(g, 250, nullptr) == PD_OK, "half of a solve");
+  for (int call = 0; call < 3; ++call) {
+    const auto density = [&](double* n) {
+      double rho = 0.0;
+      return call == 0   ? pd_snapshot(g, n, 1, &rho, nullptr)
+             : call == 1 ? pd_density(g, n, 1, &rho, nullptr)
+                         : pd_density_static(g, n, 1, &rho, nullptr);
+    };
+    if (call == 1) expect(pd_propagate(g, -1, nullptr) == PD_OK, "the rest");
+    int copies = copies_of_n;
+    expect(density(static_cast<double*>(device)) == PD_OK, "n to the device");
+    expect(last_density.n_copy == device && copies_of_n == copies, "stored by the pass");
+    elsewhere.assign(m, 0.0);
+    expect(density(elsewhere.data()) == PD_OK, "n elsewhere");
+    expect(!last_density.n_copy && copies_of_n == copies + 1 && elsewhere[m - 1] == 1.0, "copied");
+    double* odd = reinterpret_cast<double*>(static_cast<char*>(device) + 4);
+    device_blocks.insert(odd);
+    expect(density(odd) == PD_OK && !last_density.n_copy, "an address that is no multiple of 8 is copied to");
+    device_blocks.erase(odd);
+  }
+  hipFree(device);
+  pd_destroy_grid(g);
+}
+
 int main() {
   check_failed_allocations();
   check_slots();
+  check_kept_memory();
+  check_copy_of_n();
   expect(device_blocks.empty(), "all device memory is given back");
   if (!failures) std::printf("host model ok\n");
   return failures;
