@@ -127,3 +127,31 @@ def test_n_to_memory_that_only_a_copy_reaches(gpu):
             raw.zero_()
             torch.cuda.synchronize()
     s.close()
+
+
+def test_captured_pass_with_its_sum(gpu):
+    """A density pass, sum included, in a graph of the caller's (a snapshot on the way), replayed
+    between eager work of the same and of other handles: n bit for bit each time, and the
+    handle's later sums as before."""
+    import torch
+
+    g, f = wl.grid(150, 2.0), wl.sin2(0.15, 0.5, 4)
+    s = gpu.Solver.for_grid(g, "fp64").set_field(f, 800)
+    want = np.empty(150 * 150)
+    rho = s.propagate(300).snapshot(n_out=want)
+    s.rewind()
+    n, cap, graph = torch.zeros(150 * 150, dtype=torch.float64, device="cuda"), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=cap, capture_error_mode="thread_local"):
+        s.propagate(300, stream=cap)
+        s.snapshot(n_out=n, want_rho=False, stream=cap)
+    torch.cuda.synchronize()
+    for _ in range(5):
+        n.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(n.cpu().numpy(), want)
+        assert s.snapshot() == rho
+        gpu.Solver.for_grid(wl.grid(40, 1.5), "fp64").set_field(f, 100).solve()
+    del graph
+    s.close()
