@@ -741,6 +741,100 @@ int strang_form(const Grid& g, const FieldTables& t) {
   return phi <= kShearMaxAngle ? kFormShear : kFormVersine;
 }
 
+namespace {
+
+// Times of a stage of a Strang solve for one wave, ns: alone on its SIMD (`single` + `single_point`
+// per point of a lane; by rows `rows_single`), and its share of a SIMD's time among many
+// (`wave` + `point` per point of a lane; by rows `rows_wave`), the kernel by rows with the points
+// per lane it has by default, four in FP64 and one in FP32.  Measured over 860 drawn solves of
+// 1000 to 3 million points, 16 to 40000 columns and 32 to 8000 rows, each by both kernels and with
+// 1, 2, 4 and (some) 8 points per lane.
+struct StageTimes {
+  double single, single_point, wave, point, rows_single, rows_wave;
+};
+constexpr StageTimes kStageTimes[3][2][2] = {
+    // second order, fourth order; the second line with a y component
+    {{{9.6, 10.6, 2.9, 11.8, 64.0, 66.5}, {10.0, 10.4, 3.6, 11.5, 84.0, 73.0}},  // PD_FP64
+     {{12.0, 16.4, 6.5, 16.9, 86.5, 87.0}, {13.5, 15.6, 6.8, 16.8, 107.6, 95.0}}},
+    {{{7.0, 13.9, 1.7, 8.55, 22.7, 12.4}, {11.0, 13.5, 2.6, 9.0, 40.0, 13.3}},  // PD_FP32
+     {{8.3, 21.4, 3.6, 12.8, 32.9, 16.8}, {12.5, 20.5, 4.5, 13.7, 50.0, 17.8}}},
+    {{{6.8, 10.7, 3.0, 6.55, 19.6, 9.4}, {10.5, 10.4, 2.9, 6.6, 34.7, 10.2}},  // PD_FP32_FAST
+     {{8.2, 16.2, 5.6, 9.35, 25.8, 13.3}, {13.0, 15.4, 6.0, 9.4, 43.6, 14.0}}}};
+
+// Waves that the fullest SIMD works through, of `units` dealt in blocks of four to 256 compute
+// units (past eight, where blocks follow one another, their mean), and what the last of them
+// take more than their share: FP32 instructions of two waves issue together, so that one without
+// a partner takes its turn alone.
+double simd_load(long long units, bool fp32) {
+  const long long blocks = (units + 3) / 4;
+  const double n = blocks <= 8 * 256 ? (double)((blocks + 255) / 256) : (double)units / 1024.0;
+  return n + (fp32 ? std::min(0.2 * n, 0.8) : std::min(0.08 * n, 0.6));
+}
+
+// Units of a launch by columns with 2^cshift columns to a wave.
+ColumnGeometry columns_at(const Grid& g, int precision, int stages, int elliptic, int ppl, int cshift) {
+  const int pair = is_fp32(precision) ? 8 : 16, lanes = 64 >> cshift;
+  const long long bands = (g.ny + ppl - 1) / ppl;
+  const long long supers = (g.nx + (1 << kColumnSuperShift) - 1) >> kColumnSuperShift;
+  const int spaces = (1 << cshift) + (elliptic ? 1 : 0);  // columns of coefficients in the LDS
+  ColumnGeometry c{};
+  c.cshift = cshift;
+  c.segs = (int)((bands + lanes - 1) / lanes);
+  c.units = (int)((supers * c.segs) << (kColumnSuperShift - cshift));
+  c.chunk = std::min(kColumnEntries, kColumnPairBytes / pair / spaces) / stages / 4 * 4;
+  return c;
+}
+constexpr int most_columns(int stages) { return stages == 5 ? 3 : 4; }  // largest cshift
+
+// Time of a stage of a solve by columns alone on the device, ns.  A further column of a wave
+// costs it the evaluation and the reads of another column's coefficients, evaluated 64 at a time
+// (short chunks leave lanes without one: 2874 x 40 in FP64 with a y component took 137 ns a stage
+// with 16 columns to a wave, 28 steps to a chunk, and 89 by rows).
+double column_time(const Grid& g, int precision, int stages, int elliptic, int ppl, int cshift) {
+  const StageTimes& t = kStageTimes[precision][elliptic ? 1 : 0][stages == 5 ? 1 : 0];
+  const bool f32 = is_fp32(precision);
+  const ColumnGeometry c = columns_at(g, precision, stages, elliptic, ppl, cshift);
+  const int entries = c.chunk * stages;
+  const double more = ((1 << cshift) - 1) * (double)((entries + 63) / 64 * 64) / entries;
+  const double one = t.single + t.single_point * ppl + 1.8 * more;
+  const double many = t.wave + t.point * ppl + (f32 ? 1.0 : 1.5) * more;
+  return std::max(one, simd_load(c.units, f32) * many);
+}
+
+// The same by rows, with the default points per lane and blocks of 256.
+double row_time(const Grid& g, int precision, int stages, int elliptic) {
+  const StageTimes& t = kStageTimes[precision][elliptic ? 1 : 0][stages == 5 ? 1 : 0];
+  const bool f32 = is_fp32(precision);
+  const long long tile = f32 ? 256 : 1024;
+  return std::max(t.rows_single, simd_load((g.points() + tile - 1) / tile * 4, f32) * t.rows_wave);
+}
+
+// Most points per lane by columns: in FP32, eight with a y component or in the fourth order take
+// so many registers that one wave is left to a SIMD (3110 x 298 in the fourth order: 292 ns a
+// stage, 190 with four).
+int most_points(int precision, int stages, int elliptic) {
+  return is_fp32(precision) && (elliptic || stages == 5) ? 4 : 8;
+}
+
+// The points per lane of the fastest launch by columns, and its time.  Within 3%, about what the
+// times are good for, the most: the fewest waves that evaluate coefficients.
+int column_points(const Grid& g, int precision, int stages, int elliptic, double* time) {
+  double of[4], least = 0.0;
+  int count = 0;
+  for (int ppl = 1; ppl <= most_points(precision, stages, elliptic); ppl *= 2, ++count) {
+    of[count] = column_time(g, precision, stages, elliptic, ppl, 0);
+    for (int s = 1; s <= most_columns(stages); ++s)
+      of[count] = std::min(of[count], column_time(g, precision, stages, elliptic, ppl, s));
+    least = count ? std::min(least, of[count]) : of[count];
+  }
+  *time = least;
+  while (of[--count] > 1.03 * least) {
+  }
+  return 1 << count;
+}
+
+}  // namespace
+
 int column_series(const Grid& g, const FieldTables& t, int precision) {
   if (g.ny < kColumnMinRows || strang_form(g, t) != kFormShear) return 0;
   // half angles of a stage: c dt (px + A_x), and at most c dt |A_y| for the field part of a
@@ -748,9 +842,17 @@ int column_series(const Grid& g, const FieldTables& t, int precision) {
   const double aymax = std::fmax(std::fabs(t.Ay_min), std::fabs(t.Ay_max));
   const double h = t.comp.cmax * t.dt * std::fmax(t.E_max, aymax);
   if (!(h <= 0.25 * kPi)) return 0;
-  const double x = h * h, r = 4.0 * x / (kPi * kPi);
+  // By columns a step has fewer instructions, but lanes stay idle where the rows do not fill a
+  // wave's bands, and each wave evaluates its columns' coefficients: grids of a few hundred rows
+  // that give each SIMD two waves or more may be faster by rows (fast FP32 1184 x 108 x 8000
+  // steps: 0.20 ms by rows, 0.30 by columns; FP32 with a y component 147 x 1260: 0.46 and 0.60).
+  double by_columns = 0.0;
+  const int S = t.comp.stages, ell = t.elliptic ? 1 : 0;
+  column_points(g, precision, S, ell, &by_columns);
+  if (by_columns > 0.95 * row_time(g, precision, S, ell)) return 0;
   // the omitted terms, relative to the leading one: tan as in taylor_order; sin(2h)
   // alternates, so at most its first.  FP32: small against the dithering's 1/8 of a spacing.
+  const double x = h * h, r = 4.0 * x / (kPi * kPi);
   const double tol = is_fp32(precision) ? 0x1p-30 : 0x1p-56;
   for (int J : {3, 5, 8, 12, 16, 20, 24}) {
     const double e = tan_series_coef(J + 1) * std::pow(x, J) / (1.0 - r);
@@ -761,77 +863,47 @@ int column_series(const Grid& g, const FieldTables& t, int precision) {
 
 ColumnGeometry column_geometry(const Grid& g, int precision, int stages, int elliptic, int points_per_lane,
                                bool alone) {
-  const int pair = is_fp32(precision) ? 8 : 16;
-  const long long bands = (g.ny + points_per_lane - 1) / points_per_lane;
-  ColumnGeometry best{};
-  double best_cost = 0.0;
   // Fewer columns to a wave: fewer coefficients to evaluate; more: fewer lanes without a
-  // row where the bands do not fill 64 lanes.  In units of a point's step (6 FMAs, at half
-  // the rate in FP64) a column's coefficients and reads take a wave about 1/4 (FP32) or 1/8.
-  // A solve alone on the device, up to one wave a SIMD: lanes without a row cost nothing, so
-  // one column (200^2 FP64, 8000 steps, two points a lane: 0.28 ms, 0.35 with four columns).
-  for (int s = 0; s <= (stages == 5 ? 3 : 4); ++s) {
-    const int lanes = 64 >> s;
-    ColumnGeometry c{};
-    c.cshift = s;
-    c.segs = (int)((bands + lanes - 1) / lanes);
-    const long long supers = (g.nx + (1 << kColumnSuperShift) - 1) >> kColumnSuperShift;
-    c.units = (int)((supers * c.segs) << (kColumnSuperShift - s));
-    const int spaces = (1 << s) + (elliptic ? 1 : 0);  // columns of coefficients in the LDS
-    c.chunk = std::min(kColumnEntries, kColumnPairBytes / pair / spaces) / stages / 4 * 4;
-    const double waves = (double)c.segs * (double)((g.nx + (1 << s) - 1) >> s);
-    const double cost = waves * (points_per_lane + spaces * (is_fp32(precision) ? 1.0 / 4 : 1.0 / 8));
-    if (best.units == 0 || cost < best_cost) {
-      best = c;
+  // row where the bands do not fill 64 lanes.  A solve alone on the device: what is fastest;
+  // one of a batch: least issue time, a column's coefficients and reads taking a wave about 1/4
+  // (FP32) or 1/8 of a point's step.
+  int best = 0;
+  double best_cost = 0.0;
+  for (int s = 0; s <= most_columns(stages); ++s) {
+    double cost;
+    if (alone) {
+      cost = column_time(g, precision, stages, elliptic, points_per_lane, s);
+    } else {
+      const int segs = columns_at(g, precision, stages, elliptic, points_per_lane, s).segs;
+      const double waves = (double)segs * (double)((g.nx + (1 << s) - 1) >> s);
+      cost = waves * (points_per_lane + ((1 << s) + (elliptic ? 1 : 0)) * (is_fp32(precision) ? 1.0 / 4 : 1.0 / 8));
+    }
+    if (s == 0 || cost < best_cost) {
+      best = s;
       best_cost = cost;
     }
-    if (s == 0 && alone && waves <= 1024.0) break;
   }
-  return best;
+  return columns_at(g, precision, stages, elliptic, points_per_lane, best);
 }
-
-namespace {
-
-// Time of a launch of `waves` waves of `ppl` points a lane, in issue slots of a point's step:
-// the waves of the fullest of the device's 1024 SIMDs, one after another, a point's share of
-// what its lane's points have in common (`shared`, of one point's step) on top.  FP32
-// instructions of two waves issue together, so that a wave without a partner takes more than
-// its turn; at 8 points a SIMD holds two waves (FP32) at a time.
-double shape_cost(long long waves, int ppl, bool fp32, double shared) {
-  long long n = (waves + 1023) / 1024;
-  if (fp32 && ppl == 8) n += n % 2;
-  const double turns = n == 1 ? (fp32 ? 1.8 : 1.12) : n + (fp32 && n % 2 ? 0.4 : 0.0);
-  return turns * ppl * (1.0 + shared / ppl);
-}
-
-}  // namespace
 
 int auto_points_per_lane(const Grid& g, int scheme, int precision, int stages, int elliptic) {
-  const bool mid = base_scheme(scheme) == PD_SCHEME_MIDPOINT, f32 = is_fp32(precision);
-  // midpoint: the column's phase (1 of 16 instructions; with its conversion, unpaired, 4 of
-  // 36 FP32 slots), up to 4 points.  Columns: the coefficients' evaluation and reads, up to 8
-  // points; with a y component in FP32 8 would take more than half of the registers.
-  // Measured, 20000 steps, 1 / 2 / 4 / 8 points: columns FP32 256^2 0.38 / 0.64 / - / - ms,
-  // 512^2 0.85 / 0.82 / 1.11 / -, 1024^2 - / 2.99 / 2.98 / 2.80; FP64 256^2 0.44 / 0.65 / - / -,
-  // 512^2 1.26 / 1.18 / 1.14 / 1.88, 1024^2 - / 4.44 / 4.23 / 4.15; midpoint FP64 64^2 x 4000
-  // 0.15 / 0.27 / 0.51, 700 x 511 x 8000 1.71 / 1.65 / 2.05, FP32 256^2 x 4000 0.21 / 0.31 /
-  // 0.55, 1024^2 x 10000 3.24 / 3.08 / 3.00.
-  const double shared = mid ? (f32 ? 0.11 : 0.065) : (f32 ? 0.22 : 0.16);
-  const int most = mid || (f32 && elliptic) ? 4 : 8;
+  double time = 0.0;
+  if (base_scheme(scheme) != PD_SCHEME_MIDPOINT) return column_points(g, precision, stages, elliptic, &time);
+  // Midpoint.  Time of a launch in issue slots of a point's step: the waves of the fullest of the
+  // device's 1024 SIMDs, one after another, a wave without a partner (FP32 instructions of two
+  // issue together) more than its turn, and what a lane's points have in common, the column's
+  // phase (1 of 16 instructions; with its conversion, unpaired, 4 of 36 FP32 slots).
+  // Measured, 1 / 2 / 4 points: FP64 64^2 x 4000 0.15 / 0.27 / 0.51 ms, 700 x 511 x 8000 1.71 /
+  // 1.65 / 2.05; FP32 256^2 x 4000 0.21 / 0.31 / 0.55, 1024^2 x 10000 3.24 / 3.08 / 3.00.
+  const bool f32 = is_fp32(precision);
   int best = 1;
-  double best_cost = 0.0;
-  for (int ppl = 1; ppl <= most; ppl *= 2) {
-    long long waves;
-    if (mid) {
-      waves = ((g.ny + ppl - 1) / ppl * (long long)g.nx + 63) / 64;
-    } else {
-      const ColumnGeometry c = column_geometry(g, precision, stages, elliptic, ppl, true);
-      waves = c.segs * (((long long)g.nx + (1 << c.cshift) - 1) >> c.cshift);
-    }
-    const double cost = shape_cost(waves, ppl, f32, shared);
-    if (ppl == 1 || cost < best_cost) {
+  for (int ppl = 1; ppl <= 4; ppl *= 2) {
+    const long long waves = ((g.ny + ppl - 1) / ppl * (long long)g.nx + 63) / 64, n = (waves + 1023) / 1024;
+    const double turns = n == 1 ? (f32 ? 1.8 : 1.12) : n + (f32 && n % 2 ? 0.4 : 0.0);
+    const double cost = turns * (ppl + (f32 ? 0.11 : 0.065));
+    if (ppl == 1 || cost < time) {
       best = ppl;
-      best_cost = cost;
+      time = cost;
     }
   }
   return best;

@@ -179,9 +179,9 @@ constexpr double sin2_series_coef(int n) {
 //
 // Terms of the series a solve's coefficients take (3, 5, or 8 to kSeriesMax in fours), or 0 where
 // the solve runs the row kernel: a rotation form other than shears, a half angle of more
-// than pi/4, or fewer than kColumnMinRows rows.  The choice rests on the grid, the field
-// and the precision alone, never on the launch shape, so that every way to run a solve
-// gives the same bits.
+// than pi/4, fewer than kColumnMinRows rows, or a grid on which the row kernel is the faster.
+// The choice rests on the grid, the field and the precision alone, never on the launch shape,
+// so that every way to run a solve gives the same bits.
 constexpr int kSeriesMax = 28;
 constexpr int kColumnMinRows = 32;
 int column_series(const Grid& g, const FieldTables& t, int precision);

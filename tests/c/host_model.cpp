@@ -237,11 +237,68 @@ static void check_copy_of_n() {
   pd_destroy_grid(g);
 }
 
+// The kernel and the launch that a grid takes: by rows where columns would leave lanes idle or a
+// wave without a partner, and by columns every point of the grid in one lane of one wave.
+static void check_strang_kernel() {
+  struct {
+    int nx, ny, precision, scheme;
+    double ellipticity;
+    bool columns;
+  } grids[] = {{64, 64, PD_FP64, PD_SCHEME_STRANG, 0, true},         {64, 64, PD_FP32_FAST, PD_SCHEME_STRANG, 0, true},
+               {512, 512, PD_FP32, PD_SCHEME_STRANG, 0, true},       {1500, 2047, PD_FP32, PD_SCHEME_STRANG, 0, true},
+               {2048, 2048, PD_FP32_FAST, PD_SCHEME_STRANG, 0, true}, {1024, 1024, PD_FP32, PD_SCHEME_STRANG4, 0.5, true},
+               {512, 512, PD_FP64, PD_SCHEME_STRANG4, 0, true},      {400, 300, PD_FP64, PD_SCHEME_STRANG, 0, true},
+               {1184, 108, PD_FP32_FAST, PD_SCHEME_STRANG, 0, false}, {725, 76, PD_FP32_FAST, PD_SCHEME_STRANG, 0.5, false},
+               {147, 1260, PD_FP32_FAST, PD_SCHEME_STRANG, 0.5, false}, {16384, 48, PD_FP32, PD_SCHEME_STRANG, 0, false},
+               {64, 31, PD_FP64, PD_SCHEME_STRANG, 0, false}};
+  pd_field f = field();
+  for (const auto& q : grids) {
+    pd_grid g = nullptr;
+    expect(pd_create_grid(q.nx, q.ny, -2.0, 2.0, -2.0, 2.0, q.precision, q.scheme, &g) == PD_OK, "grid");
+    f.ellipticity = q.ellipticity;
+    expect(pd_set_field(g, &f, 4000) == PD_OK, "field");
+    if ((g->series != 0) != q.columns) {
+      std::printf("FAIL kernel of %d x %d precision %d scheme %d y component %g\n", q.nx, q.ny, q.precision, q.scheme,
+                  q.ellipticity);
+      ++failures;
+    }
+    pd_destroy_grid(g);
+  }
+  unsigned seed = 1;
+  const auto pick = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+  for (int trial = 0; trial < 300; ++trial) {
+    Grid g;
+    g.nx = 1 + pick(trial % 3 ? 70 : 300);
+    g.ny = kColumnMinRows + pick(trial % 2 ? 40 : 500);
+    const int precision = pick(3), stages = pick(2) ? 5 : 1, ell = pick(2), ppl = 1 << pick(4), waves = 1 << pick(3);
+    const ColumnGeometry c = column_geometry(g, precision, stages, ell, ppl, pick(2) != 0);
+    const int pair = precision == PD_FP64 ? 16 : 8, spaces = (1 << c.cshift) + ell, stride = c.chunk * stages + 16 / pair;
+    expect(c.chunk >= 4 && c.chunk % 4 == 0 && spaces * stride * pair + 256 + 16 <= kColumnLdsWave, "the wave's LDS");
+    std::vector<int> seen((size_t)g.nx * g.ny, 0);
+    const int blocks = ((c.units + waves - 1) / waves + 7) / 8 * 8, shift = kColumnSuperShift - c.cshift;
+    for (int unit = 0; unit < blocks * waves; ++unit) {  // as the kernel deals them
+      const int super_units = c.segs << shift, super = unit / super_units, rest = unit % super_units;
+      const int col0 = (super << kColumnSuperShift) + ((rest & ((1 << shift) - 1)) << c.cshift);
+      if (unit >= c.units || col0 >= g.nx) continue;
+      for (int lane = 0; lane < 64; ++lane)
+        for (int q = 0; q < ppl; ++q) {
+          const int col = col0 + (lane & ((1 << c.cshift) - 1));
+          const long long row = (long long)((rest >> shift) * (64 >> c.cshift) + (lane >> c.cshift)) * ppl + q;
+          if (col < g.nx && row < g.ny) ++seen[(size_t)row * g.nx + col];
+        }
+    }
+    bool once = true;
+    for (int n : seen) once = once && n == 1;
+    expect(once, "every point in one lane");
+  }
+}
+
 int main() {
   check_failed_allocations();
   check_slots();
   check_kept_memory();
   check_copy_of_n();
+  check_strang_kernel();
   expect(device_blocks.empty(), "all device memory is given back");
   if (!failures) std::printf("host model ok\n");
   return failures;
