@@ -15,7 +15,7 @@
 using namespace pdx;
 
 // Device descriptors of one launch sequence in one allocation that one copy fills:
-// the work counters, the solves, the work items and the density jobs, each at a
+// the work counter, the solves, the work items and the density jobs, each at a
 // 256-byte boundary; and one rho per member.
 struct BatchDescriptors {
   unsigned char* d_block = nullptr;
@@ -125,8 +125,8 @@ bool graph_current(pd_batch b) {
 
 struct Plan {
   std::vector<BatchSolve> solves;
-  std::vector<BatchItem> items;  // those of kBatchRows, then those of kBatchColumns
-  size_t kind_items[kBatchKinds] = {};
+  std::vector<BatchItem> items;
+  int kind = kBatchRows;  // the kernel for them
   std::vector<DensityJob> jobs;
   std::vector<std::pair<size_t, SolveParams>> separate;  // members run by their own launch
   long long density_tiles = 0;
@@ -198,16 +198,14 @@ pd_status make_plan(pd_batch b, double* rho_copies, const std::vector<long long>
   std::stable_sort(order.begin(), order.end(),
                    [&](size_t a, size_t c) { return end[a] - begin[a] > end[c] - begin[c]; });
   plan->items.clear();
-  for (int kind = 0; kind < kBatchKinds; ++kind) {
-    const size_t before = plan->items.size();
-    for (size_t i : order) {
-      if (batch_kind(b->grids[i]) != kind) continue;
-      long long span;
-      const long long tiles = b->grids[i]->batch_tiles(b->points_per_lane, b->block_threads, &span);
-      for (long long q = 0; q < tiles; ++q) plan->items.push_back(BatchItem{(int)i, 0, q * span});
-    }
-    plan->kind_items[kind] = plan->items.size() - before;
+  bool of_kind[2] = {};
+  for (size_t i : order) {
+    long long span;
+    const long long tiles = b->grids[i]->batch_tiles(b->points_per_lane, b->block_threads, &span);
+    for (long long q = 0; q < tiles; ++q) plan->items.push_back(BatchItem{(int)i, 0, q * span});
+    of_kind[batch_kind(b->grids[i])] = true;
   }
+  plan->kind = of_kind[kBatchRows] && of_kind[kBatchColumns] ? kBatchMixed : of_kind[kBatchColumns] ? kBatchColumns : kBatchRows;
   if (plan->items.size() > (size_t)0x7fffffff) return set_error(PD_ERR_INVALID, "too many work items");
   plan->jobs.clear();
   plan->density_tiles = 0;
@@ -256,7 +254,7 @@ pd_status upload(pd_batch b, BatchDescriptors& D, const Plan& plan, hipStream_t 
   return PD_OK;
 }
 
-// Enqueue one launch sequence on `stream`: the persistent kernels over the plan's
+// Enqueue one launch sequence on `stream`: the persistent kernel over the plan's
 // items and, concurrently on the side stream (forked from and joined back into
 // `stream` with events, so the sequence stays one stream-ordered unit and one
 // captured graph), the other members' own launches; then the batched density.
@@ -264,21 +262,15 @@ pd_status upload(pd_batch b, BatchDescriptors& D, const Plan& plan, hipStream_t 
 // leave as its queue drains.
 pd_status enqueue(pd_batch b, BatchDescriptors& D, const Plan& plan, hipStream_t stream) {
   hipError_t e;
-  const size_t* n = plan.kind_items;
-  const bool both = n[kBatchRows] && n[kBatchColumns];  // the row tiles then go beside, too
-  const bool fork = both || !plan.separate.empty();
-  if (!plan.items.empty() && (e = launch_batch_reset(D.d_counter, stream)) != hipSuccess)
-    return hip_error(e, "batch launch");
+  const bool fork = !plan.separate.empty();
   if (fork) {
     if ((e = hipEventRecord(b->fork, stream)) != hipSuccess) return hip_error(e, "hipEventRecord(fork)");
     if ((e = hipStreamWaitEvent(b->side_stream, b->fork, 0)) != hipSuccess) return hip_error(e, "hipStreamWaitEvent");
   }
-  for (int kind = 0; kind < kBatchKinds; ++kind) {
-    if (!n[kind]) continue;
-    const BatchItem* items = D.d_items + (kind == kBatchColumns ? n[kBatchRows] : 0);
-    const long long blocks = std::min<long long>(persistent_slots(b, kind), (long long)n[kind]);
-    e = launch_batch(kind, b->points_per_lane, b->block_threads, (int)blocks, D.d_solves, items, (int)n[kind],
-                     D.d_counter + kind, both && kind == kBatchRows ? b->side_stream : stream);
+  if (!plan.items.empty()) {
+    const long long blocks = std::min<long long>(persistent_slots(b, plan.kind), (long long)plan.items.size());
+    e = launch_batch(plan.kind, b->points_per_lane, b->block_threads, (int)blocks, D.d_solves, D.d_items,
+                     (int)plan.items.size(), D.d_counter, stream);
     if (e != hipSuccess) return hip_error(e, "batch launch");
   }
   // the other members: the single-solve kernels, exactly as a solve alone

@@ -424,8 +424,40 @@ __global__ void __launch_bounds__(256) strang_kernel(const SolveParams p) {
 // in the single-solve kernel, so each solve's result does not depend on the
 // batch it runs in.
 
-__global__ void batch_reset(unsigned int* counters) {
-  if (blockIdx.x == 0 && threadIdx.x < kBatchKinds) counters[threadIdx.x] = 0u;
+__global__ void batch_reset(unsigned int* counter) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;
+}
+
+// A tile of a solve by rows: the block's points from `base`.
+template <int PPL>
+__device__ __forceinline__ void batch_rows(const BatchSolve& s, long long base) {
+  if (s.precision == PD_FP32) {
+    if (s.form == kFormShear)
+      strang_tile<float, PPL, 0, kFormShear, 1, 0, kShearOnce>(s.p, base);
+    else
+      strang_tile<float, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
+  } else if (s.precision == PD_FP32_FAST) {
+    if (s.form == kFormShear)
+      strang_tile<float, PPL, 0, kFormShear, 1, 0, kShearAlt>(s.p, base);
+    else
+      strang_tile<float, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
+  } else {
+    if (s.form == kFormShear)
+      strang_tile<double, PPL, 0, kFormShear, 1, 0, kShearPlain>(s.p, base);
+    else
+      strang_tile<double, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
+  }
+}
+
+// A wave's unit of a solve by columns.
+template <int PPL>
+__device__ __forceinline__ void batch_columns(const BatchSolve& s, int unit, unsigned char* lds) {
+  if (s.precision == PD_FP32)
+    column_tile<float, PPL, 1, 0, kShearOnce>(s.p, unit, lds);
+  else if (s.precision == PD_FP32_FAST)
+    column_tile<float, PPL, 1, 0, kShearAlt>(s.p, unit, lds);
+  else
+    column_tile<double, PPL, 1, 0, kShearPlain>(s.p, unit, lds);
 }
 
 template <int PPL>
@@ -440,24 +472,7 @@ __global__ void __launch_bounds__(256) batch_kernel(const BatchSolve* __restrict
     const int it = next;
     if (it >= n_items) return;  // uniform over the block
     const BatchItem w = items[it];
-    const BatchSolve& s = solves[w.solve];
-    const long long base = w.base + threadIdx.x;
-    if (s.precision == PD_FP32) {
-      if (s.form == kFormShear)
-        strang_tile<float, PPL, 0, kFormShear, 1, 0, kShearOnce>(s.p, base);
-      else
-        strang_tile<float, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
-    } else if (s.precision == PD_FP32_FAST) {
-      if (s.form == kFormShear)
-        strang_tile<float, PPL, 0, kFormShear, 1, 0, kShearAlt>(s.p, base);
-      else
-        strang_tile<float, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
-    } else {
-      if (s.form == kFormShear)
-        strang_tile<double, PPL, 0, kFormShear, 1, 0, kShearPlain>(s.p, base);
-      else
-        strang_tile<double, PPL, 0, kFormVersine, 1, 0, kShearPlain>(s.p, base);
-    }
+    batch_rows<PPL>(solves[w.solve], w.base + threadIdx.x);
   }
 }
 
@@ -481,14 +496,32 @@ __global__ void __launch_bounds__(256, 4) batch_columns_kernel(const BatchSolve*
     if (it >= n_items) return;
     const BatchItem w = items[it];
     const BatchSolve s = solves[w.solve];
-    unsigned char* lds = pd_lds + wave * kColumnLdsWave;
-    const int unit = (int)w.base + wave;
-    if (s.precision == PD_FP32)
-      column_tile<float, PPL, 1, 0, kShearOnce>(s.p, unit, lds);
-    else if (s.precision == PD_FP32_FAST)
-      column_tile<float, PPL, 1, 0, kShearAlt>(s.p, unit, lds);
-    else
-      column_tile<double, PPL, 1, 0, kShearPlain>(s.p, unit, lds);
+    batch_columns<PPL>(s, (int)w.base + wave, pd_lds + wave * kColumnLdsWave);
+  }
+}
+
+// Items of both kinds from one queue.  Two kernels side by side, one of each kind, had their
+// blocks dealt to the same compute units while others stood idle.
+template <int PPL>
+__global__ void __launch_bounds__(256, 3) batch_mixed_kernel(const BatchSolve* __restrict__ solves,
+                                                             const BatchItem* __restrict__ items, int n_items,
+                                                             unsigned int* counter) {
+  __shared__ int next;
+  extern __shared__ __align__(16) unsigned char pd_lds[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (;;) {
+    __syncthreads();  // every lane has read the previous item index
+    if (threadIdx.x == 0) next = (int)atomicAdd(counter, 1u);
+    __syncthreads();
+    const int it = __builtin_amdgcn_readfirstlane(next);
+    if (it >= n_items) return;
+    const BatchItem w = items[it];
+    if (solves[w.solve].p.series) {
+      const BatchSolve s = solves[w.solve];
+      batch_columns<PPL>(s, (int)w.base + wave, pd_lds + wave * kColumnLdsWave);
+    } else {
+      batch_rows<PPL>(solves[w.solve], w.base + threadIdx.x);
+    }
   }
 }
 
@@ -1265,23 +1298,23 @@ hipError_t launch_batch_density(const DensityJob* jobs, int n_jobs, long long to
 }
 
 namespace {
-size_t batch_lds(int kind, int block) { return kind == kBatchColumns ? (size_t)(block / 64) * kColumnLdsWave : 0; }
+size_t batch_lds(int kind, int block) { return kind == kBatchRows ? 0 : (size_t)(block / 64) * kColumnLdsWave; }
 
 using BatchKernel = void (*)(const BatchSolve*, const BatchItem*, int, unsigned int*);
 BatchKernel batch_kernel_of(int kind, int ppl) {
   if (kind == kBatchColumns)
     return ppl == 1 ? batch_columns_kernel<1> : ppl == 2 ? batch_columns_kernel<2> : batch_columns_kernel<4>;
+  if (kind == kBatchMixed)
+    return ppl == 1 ? batch_mixed_kernel<1> : ppl == 2 ? batch_mixed_kernel<2> : batch_mixed_kernel<4>;
   return ppl == 1 ? batch_kernel<1> : ppl == 2 ? batch_kernel<2> : batch_kernel<4>;
 }
 }  // namespace
 
-hipError_t launch_batch_reset(unsigned int* counters, hipStream_t stream) {
-  hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, stream, counters);
-  return hipGetLastError();
-}
-
 hipError_t launch_batch(int kind, int ppl, int block, int grid_blocks, const BatchSolve* solves,
                         const BatchItem* items, int n_items, unsigned int* counter, hipStream_t stream) {
+  hipLaunchKernelGGL(batch_reset, dim3(1), dim3(64), 0, stream, counter);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(batch_kernel_of(kind, ppl), dim3(grid_blocks), dim3(block), batch_lds(kind, block), stream, solves,
                      items, n_items, counter);
   return hipGetLastError();

@@ -321,10 +321,9 @@ constexpr long long kStaticPartials = kStaticMaxPoints / 2048;
 // Device address of the static scratch on `device` (kStaticPartials partials, then
 // one sum), looked up on the first call for that device.
 hipError_t static_scratch(int device, double** out);
-// The persistent kernels of a batch: tiles of the row kernel, and waves' units of the
-// column kernels.  Each has its own work items and its own counter.
-constexpr int kBatchRows = 0, kBatchColumns = 1, kBatchKinds = 2;
-hipError_t launch_batch_reset(unsigned int* counters, hipStream_t stream);
+// The persistent kernels of a batch, for items by rows (tiles of points), by columns (waves'
+// units) and of both kinds.  launch_batch clears the counter first.
+constexpr int kBatchRows = 0, kBatchColumns = 1, kBatchMixed = 2, kBatchKinds = 3;
 hipError_t launch_batch(int kind, int points_per_lane, int block_threads, int grid_blocks, const BatchSolve* solves,
                         const BatchItem* items, int n_items, unsigned int* counter, hipStream_t stream);
 hipError_t launch_batch_density(const DensityJob* jobs, int n_jobs, long long total_tiles, hipStream_t stream);
