@@ -35,7 +35,6 @@ import argparse
 import ctypes
 import hashlib
 import json
-import math
 import os
 import sys
 import time
@@ -57,13 +56,11 @@ METRIC = "momentum point-steps/s (FP32 vs FP64 form) at stated n(p) error; p50/p
 FORM_NAMES = {"fp32": "FP32", "fp32fast": "fast FP32", "fp64": "FP64"}
 ALGO = {(0, "fp64"): (18, 18, 9), (0, "fp32"): (18, 21, 12), (0, "fp32fast"): (18, 17, 9),
         (1, "fp64"): (24, 24, 12), (1, "fp32"): (24, 24, 18), (1, "fp32fast"): (24, 24, 18)}
-# The kernel by columns (grids of at least 32 rows, shear form) applies the field's and the
+# The kernel by columns (info's by_columns) applies the field's and the
 # point's rotation about x as one: two rotations of three FMAs a step.  PD_FP32 rounds each
 # component once per rotation (one add more each).  A y component adds its field rotation:
 # three FMAs, an add more in PD_FP32; the fast form merges it into the point's (five FMAs and
 # an add for two).
-COLUMN_ROWS = 32
-FOURTH_ORDER_STAGE = 4 / (4 - 4 ** (1 / 3)) - 1  # its longest stage, of a step
 # (y component, precision) -> as ALGO
 COLUMNS = {(0, "fp64"): (12, 12, 6), (0, "fp32"): (12, 14, 8), (0, "fp32fast"): (12, 12, 6),
            (1, "fp64"): (18, 18, 9), (1, "fp32"): (18, 21, 12), (1, "fp32fast"): (18, 17, 9)}
@@ -118,12 +115,10 @@ def algo(info: dict, precision: str):
     return stages * flops, stages * flops, stages * instr
 
 
-def solve_work(info: dict, precision: str, ny: int):
-    """algo() for a solve of ny rows: what its kernel, by columns (shears, at least 32 rows, half
-    angles up to pi/4) or by rows, does."""
-    stages = info.get("stages", 1) or 1
-    half = info["dt"] * info["E_max"] * (FOURTH_ORDER_STAGE if stages == 5 else 1.0)
-    if info["scheme"] in (0, 2) and info["rotation_form"] == 0 and ny >= COLUMN_ROWS and half <= 0.25 * math.pi:
+def solve_work(info: dict, precision: str):
+    """algo() of a solve: what its kernel, by columns or by rows, does."""
+    if info.get("by_columns"):
+        stages = info.get("stages", 1) or 1
         return tuple(stages * v for v in COLUMNS[(1 if info.get("elliptic") else 0, precision)])
     return algo(info, precision)
 
@@ -266,6 +261,9 @@ def batch_object(args, pd, torch, np):
         solvers.append(s)
     total = float(sum(c["grid"]["nx"] * c["grid"]["ny"] * c["n_steps"] for c in cfgs))
     forms = {s.info()["rotation_form"] for s in solvers}
+    # work per point-step, the members' mean
+    work = [[w * s.nx * s.ny * s.n_steps / total for w in solve_work(s.info(), prec)] for s in solvers]
+    algo_flop, exec_flop, instr = (sum(w) for w in zip(*work))
     st = torch.cuda.Stream()
     b = pd.Batch(solvers)
     t_tune = time.perf_counter()
@@ -327,7 +325,6 @@ def batch_object(args, pd, torch, np):
     b.close()
     for s in solvers:
         s.close()
-    algo_flop, exec_flop, instr = COLUMNS[(0, prec)]
     algo_flop = min(algo_flop, exec_flop)
     achieved = algo_flop * total / (dev_ms * 1e-3) / 1e12
     out = {
@@ -701,7 +698,7 @@ def main():
     t = main_form["t_total"]
     value = ps_per_solve * K / t
     kern_ms = float(np.mean(main_form["kernel_ms"]))
-    flop_a, flop_e, instr = solve_work(main_form["info"], args.precision, c["grid"]["ny"])
+    flop_a, flop_e, instr = solve_work(main_form["info"], args.precision)
     flop_a = min(flop_a, flop_e)  # never more than the kernel executes
     achieved = flop_a * ps_per_solve / (kern_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.precision]
@@ -758,7 +755,7 @@ def main():
     }
     if other is not None:
         okm = float(np.mean(other["kernel_ms"]))
-        fa64, fe64, i64 = solve_work(other["info"], "fp64", c["grid"]["ny"])
+        fa64, fe64, i64 = solve_work(other["info"], "fp64")
         fa64 = min(fa64, fe64)
         line["fp64_form"] = {
             "value": ps_per_solve * K / other["t_total"], "ms_per_step": other["t_total"] / K * 1e3,
@@ -768,7 +765,7 @@ def main():
             "valu_issue_frac": i64 * ps_per_solve / (okm * 1e-3) / (CU_CLOCKS_PER_S * LANES_PER_CLK["fp64"])}
     if fast is not None:
         fkm = float(np.mean(fast["kernel_ms"]))
-        faf, fef, fi = solve_work(fast["info"], alt_prec, c["grid"]["ny"])
+        faf, fef, fi = solve_work(fast["info"], alt_prec)
         faf = min(faf, fef)
         line["fp32_fast_form" if alt_prec == "fp32fast" else "fp32_once_form"] = {
             "value": ps_per_solve * K / fast["t_total"], "ms_per_step": fast["t_total"] / K * 1e3,

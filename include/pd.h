@@ -152,10 +152,7 @@ typedef struct {
                                solve's kernel reads its table so (pd_set_launch) */
   int chunk_steps;
   int rotation_form;        /* Strang: 0 = three shears per rotation (every rotation angle of the
-                               solve <= pi/2), 1 = versine form (h = cos - 1, s = sin).  Form 0 on
-                               at least 32 rows, with dt |p + A| (0.66 of it in the fourth order)
-                               at most pi/4, runs by columns: the field's and the point's rotation
-                               about x as one.
+                               solve <= pi/2), 1 = versine form (h = cos - 1, s = sin).
                                Midpoint: 0 = tangent form (the step divided by cos(dt E), one
                                series; chosen when the state's growth over 1024 steps stays
                                below 2^32), 1 = cosine form (cos - 1 and sin(x)/x) */
@@ -167,6 +164,9 @@ typedef struct {
   int valley;               /* pd_valley */
   int stages;               /* second-order steps per step: 1, or 5 for the fourth-order schemes */
   int elliptic;             /* 1 if the field has a y component */
+  int by_columns;           /* Strang: 1 = by columns, the field's and the point's rotation about x as
+                               one (form 0, at least 32 rows, half angles c dt |p + A| of at most
+                               pi/4, and a grid on which that is the faster); 0 = by rows */
   double Ay_in, Ay_out;     /* A_y(t_i), A_y(t_f) */
 } pd_info;
 
@@ -326,7 +326,7 @@ pd_status pd_load_state(pd_grid g, const void* host, size_t bytes, long long ste
    a power of two in [64, 4096] (at most 1024 in the FP32 form, whose
    renormalisation period it must divide); a solve whose chunk of rows would
    exceed 64 KiB of LDS (long rows: fourth order, y component) reads them with the
-   scalar unit instead.  A Strang solve by columns (pd_info.rotation_form) keeps coefficients
+   scalar unit instead.  A Strang solve by columns (pd_info.by_columns) keeps coefficients
    of its own in the LDS whatever the stage and the chunk; its points per lane, if never
    set, follow the grid's size.  0 keeps the current value.  Results do not depend on the
    launch shape (bit for bit). */

@@ -82,6 +82,7 @@ class pd_info(ctypes.Structure):
         ("valley", ctypes.c_int),
         ("stages", ctypes.c_int),
         ("elliptic", ctypes.c_int),
+        ("by_columns", ctypes.c_int),
         ("Ay_in", ctypes.c_double),
         ("Ay_out", ctypes.c_double),
     ]

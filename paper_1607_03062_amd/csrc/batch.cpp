@@ -155,10 +155,10 @@ long long persistent_slots(pd_batch b, int kind) {
 // scheduled by the hardware) then runs at the rate of the solve alone, where the persistent
 // kernel's equal items would leave a partly filled last round of blocks (rows: a lone
 // 2048^2 member in a 3000-step epoch ran at 0.90 of that rate, against 0.96 in its own
-// launch).  By columns a 1024^2 member, 1024 tiles for 1024 resident blocks, is as fast
-// among the items as by itself (epochs of 3000 steps, own / among: alone 0.57 / 0.57 ms, with
-// three small members 0.86 / 0.74), and whole solves of three of them and thirteen smaller
-// ones pack better: 3.70 / 3.35 ms.
+// launch).  By columns a 1024^2 FP32 member, 1024 tiles for 1024 resident blocks, is as fast
+// among the items as by itself (epochs of 3000 steps, own / among: alone 0.57 / 0.58 ms, with
+// three small members 0.70 / 0.68, two of them with a small one 1.14 / 1.05), and whole solves
+// of three of them and thirteen smaller ones pack better: 2.61 / 2.49 ms.
 bool persistent_member(pd_batch b, pd_grid g) {
   if (g->scheme != PD_SCHEME_STRANG || g->field.elliptic) return false;
   long long span;

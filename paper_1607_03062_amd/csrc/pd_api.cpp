@@ -345,6 +345,8 @@ void fill_info(pd_grid g, const FieldTables& t, long long masked, long long step
   out->valley = g->valley;
   out->stages = composition_of(g->scheme).stages;
   out->elliptic = t.elliptic ? 1 : 0;
+  if (base_scheme(g->scheme) == PD_SCHEME_STRANG && t.n_steps > 0)
+    out->by_columns = column_series(g->grid, t, g->precision) ? 1 : 0;
   out->Ay_in = t.Ay_in;
   out->Ay_out = t.Ay_out;
 }

@@ -46,19 +46,13 @@ def test_strang_work_per_point_step():
 
 
 def test_work_follows_the_kernel_that_runs():
-    """By columns from 32 rows and up to half angles of pi/4, by rows otherwise."""
-    info = {"scheme": 0, "rotation_form": 0, "stages": 1, "elliptic": 0, "dt": 0.01, "E_max": 5.0}
-    assert bench.solve_work(info, "fp64", 32) == (12, 12, 6)
-    assert bench.solve_work(info, "fp32", 32) == (12, 14, 8)
-    assert bench.solve_work(info, "fp32fast", 32) == (12, 12, 6)
-    assert bench.solve_work(dict(info, elliptic=1, stages=5), "fp32", 32) == (90, 105, 60)
-    assert bench.solve_work(info, "fp64", 31) == bench.algo(info, "fp64")
-    assert bench.solve_work(dict(info, rotation_form=1), "fp64", 32) == bench.algo(dict(info, rotation_form=1), "fp64")
-    large = dict(info, dt=0.16)  # 0.8, past pi/4, which the fourth order's stages are not
-    assert bench.solve_work(large, "fp64", 32) == bench.algo(large, "fp64")
-    assert bench.solve_work(dict(large, stages=5), "fp64", 32) == (60, 60, 30)
-    larger = dict(large, dt=0.25, stages=5)
-    assert bench.solve_work(larger, "fp64", 32) == bench.algo(larger, "fp64")
+    info = {"scheme": 0, "rotation_form": 0, "stages": 1, "elliptic": 0, "by_columns": 1}
+    assert bench.solve_work(info, "fp64") == (12, 12, 6)
+    assert bench.solve_work(info, "fp32") == (12, 14, 8)
+    assert bench.solve_work(info, "fp32fast") == (12, 12, 6)
+    assert bench.solve_work(dict(info, elliptic=1, stages=5), "fp32") == (90, 105, 60)
+    for by_rows in (dict(info, by_columns=0), dict(info, by_columns=0, rotation_form=1)):
+        assert bench.solve_work(by_rows, "fp64") == bench.algo(by_rows, "fp64")
 
 
 def test_midpoint_work_per_point_step():
