@@ -166,7 +166,8 @@ typedef struct {
   int elliptic;             /* 1 if the field has a y component */
   int by_columns;           /* Strang: 1 = by columns, the field's and the point's rotation about x as
                                one (form 0, at least 32 rows, half angles c dt |p + A| of at most
-                               pi/4, and a grid on which that is the faster); 0 = by rows */
+                               pi/4, and a grid on which a solve of a new field is not faster
+                               by rows); 0 = by rows */
   double Ay_in, Ay_out;     /* A_y(t_i), A_y(t_f) */
 } pd_info;
 

@@ -77,6 +77,7 @@ pd_status apply(pd_grid g, const Shape& s) {
   if (r == PD_OK && eight) {
     g->points_per_lane = 8;
     g->points_chosen = true;
+    g->choose_shape();
   }
   return r;
 }

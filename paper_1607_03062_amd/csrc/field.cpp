@@ -748,7 +748,8 @@ namespace {
 // (`wave` + `point` per point of a lane; by rows `rows_wave`), the kernel by rows with the points
 // per lane it has by default, four in FP64 and one in FP32.  Measured over 860 drawn solves of
 // 1000 to 3 million points, 16 to 40000 columns and 32 to 8000 rows, each by both kernels and with
-// 1, 2, 4 and (some) 8 points per lane.
+// 1, 2, 4 and (some) 8 points per lane, in repeated passes of the step loop.  The faster of the two
+// kernels by them was within 5% of the faster one on all but 9 of 1100 further solves.
 struct StageTimes {
   double single, single_point, wave, point, rows_single, rows_wave;
 };
@@ -816,7 +817,7 @@ int most_points(int precision, int stages, int elliptic) {
   return is_fp32(precision) && (elliptic || stages == 5) ? 4 : 8;
 }
 
-// The points per lane of the fastest launch by columns, and its time.  Within 3%, about what the
+// The points per lane of the fastest launch by columns, and its time.  Within 2%, less than the
 // times are good for, the most: the fewest waves that evaluate coefficients.
 int column_points(const Grid& g, int precision, int stages, int elliptic, double* time) {
   double of[4], least = 0.0;
@@ -828,7 +829,7 @@ int column_points(const Grid& g, int precision, int stages, int elliptic, double
     least = count ? std::min(least, of[count]) : of[count];
   }
   *time = least;
-  while (of[--count] > 1.03 * least) {
+  while (of[--count] > 1.02 * least) {
   }
   return 1 << count;
 }
@@ -843,13 +844,19 @@ int column_series(const Grid& g, const FieldTables& t, int precision) {
   const double h = t.comp.cmax * t.dt * std::fmax(t.E_max, aymax);
   if (!(h <= 0.25 * kPi)) return 0;
   // By columns a step has fewer instructions, but lanes stay idle where the rows do not fill a
-  // wave's bands, and each wave evaluates its columns' coefficients: grids of a few hundred rows
-  // that give each SIMD two waves or more may be faster by rows (fast FP32 1184 x 108 x 8000
-  // steps: 0.20 ms by rows, 0.30 by columns; FP32 with a y component 147 x 1260: 0.46 and 0.60).
+  // wave's bands, and each wave evaluates its columns' coefficients: the step loop of some grids
+  // is faster by rows (fast FP32 1184 x 108 x 8000 steps: 0.20 ms by rows, 0.30 by columns).  A
+  // new field costs the row kernel more, though: a sine and a cosine a step and a column on the
+  // host (15 ns a step, 27 with a y component, 40 and 14 a column), and its scalar unit waits
+  // for rows that no pass has brought near yet (18 and 35 ns a step).  What counts is the call
+  // with a new field (1403 x 38 x 14714 in FP32 with a y component: 2.47 ms by rows, 0.72 by
+  // columns, of which 0.50 and 0.63 the step loop).
   double by_columns = 0.0;
   const int S = t.comp.stages, ell = t.elliptic ? 1 : 0;
+  const double n = (double)t.n_steps * S;
+  const double set_up = n * (ell ? 62.0 : 33.0) + (double)g.nx * (S == 5 ? 2 : 1) * (is_fp32(precision) ? 40.0 : 14.0);
   column_points(g, precision, S, ell, &by_columns);
-  if (by_columns > 0.95 * row_time(g, precision, S, ell)) return 0;
+  if (n * by_columns > 0.95 * n * row_time(g, precision, S, ell) + set_up) return 0;
   // the omitted terms, relative to the leading one: tan as in taylor_order; sin(2h)
   // alternates, so at most its first.  FP32: small against the dithering's 1/8 of a spacing.
   const double x = h * h, r = 4.0 * x / (kPi * kPi);
@@ -892,15 +899,16 @@ int auto_points_per_lane(const Grid& g, int scheme, int precision, int stages, i
   // Midpoint.  Time of a launch in issue slots of a point's step: the waves of the fullest of the
   // device's 1024 SIMDs, one after another, a wave without a partner (FP32 instructions of two
   // issue together) more than its turn, and what a lane's points have in common, the column's
-  // phase (1 of 16 instructions; with its conversion, unpaired, 4 of 36 FP32 slots).
+  // phase (with its conversion, unpaired, 4 of 36 FP32 slots; FP64 as measured on large grids).
   // Measured, 1 / 2 / 4 points: FP64 64^2 x 4000 0.15 / 0.27 / 0.51 ms, 700 x 511 x 8000 1.71 /
-  // 1.65 / 2.05; FP32 256^2 x 4000 0.21 / 0.31 / 0.55, 1024^2 x 10000 3.24 / 3.08 / 3.00.
+  // 1.65 / 2.05, 22403 x 249 x 5377 - / 17.8 / 17.1; FP32 256^2 x 4000 0.21 / 0.31 / 0.55,
+  // 1024^2 x 10000 3.24 / 3.08 / 3.00.
   const bool f32 = is_fp32(precision);
   int best = 1;
   for (int ppl = 1; ppl <= 4; ppl *= 2) {
     const long long waves = ((g.ny + ppl - 1) / ppl * (long long)g.nx + 63) / 64, n = (waves + 1023) / 1024;
     const double turns = n == 1 ? (f32 ? 1.8 : 1.12) : n + (f32 && n % 2 ? 0.4 : 0.0);
-    const double cost = turns * (ppl + (f32 ? 0.11 : 0.065));
+    const double cost = turns * (ppl + (f32 ? 0.11 : 0.14));
     if (ppl == 1 || cost < time) {
       best = ppl;
       time = cost;

@@ -477,8 +477,9 @@ __global__ void __launch_bounds__(256) batch_kernel(const BatchSolve* __restrict
 }
 
 // The same for solves by columns, in a kernel of its own: its 128 registers let four blocks
-// of 256 threads stay on a compute unit, where both kinds of tile in one kernel took 178 and
-// held two.  Sixteen FP32 solves of 128^2 to 1024^2 points: 5.9 ms by rows, 4.2 by columns.
+// of 256 threads stay on a compute unit, where both kinds of tile in one kernel take 168 and
+// let three.  Sixteen FP32 solves of 128^2 to 1024^2 points, whole passes: 5.55 ms by rows, 4.07
+// by columns.
 template <int PPL>
 __global__ void __launch_bounds__(256, 4) batch_columns_kernel(const BatchSolve* __restrict__ solves,
                                                                const BatchItem* __restrict__ items, int n_items,
@@ -501,7 +502,9 @@ __global__ void __launch_bounds__(256, 4) batch_columns_kernel(const BatchSolve*
 }
 
 // Items of both kinds from one queue.  Two kernels side by side, one of each kind, had their
-// blocks dealt to the same compute units while others stood idle.
+// blocks dealt to the same compute units while others stood idle: six solves of 138 x 207 to
+// 208 x 460 points in three precisions, two of them by rows, 0.66 ms, all by rows 0.47, from one
+// queue 0.44.
 template <int PPL>
 __global__ void __launch_bounds__(256, 3) batch_mixed_kernel(const BatchSolve* __restrict__ solves,
                                                              const BatchItem* __restrict__ items, int n_items,

@@ -217,7 +217,7 @@ SolveParams pd_grid_s::solve_params(long long k_begin, long long k_end, void* st
   p.form = form;
   p.tan = tan;
   p.series = series;
-  if (series) p.columns = columns(shape_points(), true);
+  if (series) p.columns = own_columns;
   return p;
 }
 
@@ -549,6 +549,7 @@ pd_status pd_set_field(pd_grid g, const pd_field* f, long long n_steps) {
   g->row_offset = row_offset;
   g->steps_done = 0;
   g->field_set = true;
+  g->choose_shape();
   g->version = next_version();
   return ok();
 }
@@ -655,6 +656,7 @@ pd_status pd_set_launch(pd_grid g, int points_per_lane, int block_threads, int t
   if (block_threads) g->block_threads = block_threads;
   if (table_stage) g->table_stage = table_stage;
   if (chunk_steps) g->chunk_steps = chunk_steps;
+  if (g->field_set) g->choose_shape();
   g->version = next_version();
   return ok();
 }

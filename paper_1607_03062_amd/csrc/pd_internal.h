@@ -179,10 +179,14 @@ constexpr double sin2_series_coef(int n) {
 //
 // Terms of the series a solve's coefficients take (3, 5, or 8 to kSeriesMax in fours), or 0 where
 // the solve runs the row kernel: a rotation form other than shears, a half angle of more
-// than pi/4, fewer than kColumnMinRows rows, or a grid on which the row kernel is the faster.
+// than pi/4, fewer than kColumnMinRows rows, or a grid on which a new field's solve is the
+// faster by rows.
 // The choice rests on the grid, the field and the precision alone, never on the launch shape,
 // so that every way to run a solve gives the same bits.
 constexpr int kSeriesMax = 28;
+// The least rows of the grids both kernels were compared on for kStageTimes.  Thinner ones run by
+// rows whatever is faster: 8000 steps of 1024 x 16 take 0.52 / 0.19 ms (rows / columns) in FP64,
+// 0.195 / 0.184 in FP32, of 16384 x 16 0.63 / 0.68 and 0.50 / 0.55.
 constexpr int kColumnMinRows = 32;
 int column_series(const Grid& g, const FieldTables& t, int precision);
 
@@ -340,6 +344,8 @@ struct pd_grid_s {
   int scheme = PD_SCHEME_STRANG;
   int points_per_lane = 2;
   bool points_chosen = false;  // points_per_lane set by the caller or the autotuner
+  int auto_points = 1;         // else what the field's solve runs with (by columns, midpoint)
+  pdx::ColumnGeometry own_columns{};  // by columns: the solve's own launch
   int block_threads = 256;
   int table_stage = 2;  // 1: LDS chunks, 2: scalar-unit reads
   int chunk_steps = 512;
@@ -397,13 +403,18 @@ struct pd_grid_s {
   // for one that runs another kernel, which has none for it).
   int shape_points() const {
     const int set = series ? points_per_lane : std::min(points_per_lane, 4);
-    if (points_chosen || !field_set) return set;
-    if (!series && pdx::base_scheme(scheme) != PD_SCHEME_MIDPOINT) return set;
-    return pdx::auto_points_per_lane(grid, scheme, precision, field.comp.stages, field.elliptic ? 1 : 0);
+    const bool own = points_chosen || !field_set || (!series && pdx::base_scheme(scheme) != PD_SCHEME_MIDPOINT);
+    return own ? set : auto_points;
   }
   // alone: the solve's own launch; else a member of a batch's persistent launch
   pdx::ColumnGeometry columns(int ppl, bool alone) const {
     return pdx::column_geometry(grid, precision, field.comp.stages, field.elliptic ? 1 : 0, ppl, alone);
+  }
+  // The launch of the current field, kept for its propagations; called where the field or the
+  // points per lane change.
+  void choose_shape() {
+    auto_points = pdx::auto_points_per_lane(grid, scheme, precision, field.comp.stages, field.elliptic ? 1 : 0);
+    if (series) own_columns = columns(shape_points(), true);
   }
   // Work items of the persistent batch kernel and the step from one's base to the next's
   long long batch_tiles(int ppl, int block, long long* span) const {

@@ -237,8 +237,8 @@ static void check_copy_of_n() {
   pd_destroy_grid(g);
 }
 
-// The kernel and the launch that a grid takes: by rows where columns would leave lanes idle or a
-// wave without a partner, and by columns every point of the grid in one lane of one wave.
+// The kernel and the launch that a grid takes: by rows where columns would lose more to idle lanes
+// than a new field costs by rows, and by columns every point of the grid in one lane of one wave.
 static void check_strang_kernel() {
   struct {
     int nx, ny, precision, scheme;
@@ -248,8 +248,8 @@ static void check_strang_kernel() {
                {512, 512, PD_FP32, PD_SCHEME_STRANG, 0, true},       {1500, 2047, PD_FP32, PD_SCHEME_STRANG, 0, true},
                {2048, 2048, PD_FP32_FAST, PD_SCHEME_STRANG, 0, true}, {1024, 1024, PD_FP32, PD_SCHEME_STRANG4, 0.5, true},
                {512, 512, PD_FP64, PD_SCHEME_STRANG4, 0, true},      {400, 300, PD_FP64, PD_SCHEME_STRANG, 0, true},
-               {1184, 108, PD_FP32_FAST, PD_SCHEME_STRANG, 0, false}, {725, 76, PD_FP32_FAST, PD_SCHEME_STRANG, 0.5, false},
-               {147, 1260, PD_FP32_FAST, PD_SCHEME_STRANG, 0.5, false}, {16384, 48, PD_FP32, PD_SCHEME_STRANG, 0, false},
+               {1184, 108, PD_FP32_FAST, PD_SCHEME_STRANG, 0, true},  {1403, 38, PD_FP32, PD_SCHEME_STRANG, 0.5, true},
+               {28762, 35, PD_FP64, PD_SCHEME_STRANG, 0, false},      {18179, 129, PD_FP32, PD_SCHEME_STRANG4, 0.5, false},
                {64, 31, PD_FP64, PD_SCHEME_STRANG, 0, false}};
   pd_field f = field();
   for (const auto& q : grids) {
