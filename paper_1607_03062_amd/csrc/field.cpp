@@ -983,7 +983,8 @@ TanPolynomial tan_polynomial(double x_max, int precision) {
       power *= x_max;
     }
     const double bound = (double)(deriv * std::pow(0.25L * x_max, m + 1) * 2.0L * x_max);
-    if (bound > tol && J == taylor) return p;
+    // of two FP32 terms always the series' own, which the kernel has as a literal: 2^-27 holds there
+    if (J == taylor && (bound > tol || (f32 && J == 2))) return p;
     if (bound > tol && o + 1 < count) continue;
     // Newton's divided differences at the nodes, expanded
     long double node[kTanTermsMax], diff[kTanTermsMax], c[kTanTermsMax] = {};

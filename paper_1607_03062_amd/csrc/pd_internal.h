@@ -227,7 +227,8 @@ int taylor_order(double x_max, int precision, int form);
 // stay well below the rounding of one.  The Taylor coefficients where as few of them reach that
 // (or reach taylor_order's bound and an interpolating polynomial takes no fewer), else those of
 // the polynomial that interpolates on the Chebyshev nodes of [0, x_max], which spreads the error
-// over the interval and needs up to four terms fewer (FP64, angles .054 to .09: 6 for 10).
+// over the interval and needs up to four terms fewer (FP64, angles .054 to .09: 6 for 10).  Two
+// FP32 terms are always the series' own, a literal in the kernel (2^-27).
 constexpr int kTanTermsMax = 8;
 struct TanPolynomial {
   int terms;  // FP32: 2, 3, 4, 5; FP64: 4, 5, 6, 8

@@ -293,7 +293,21 @@ static void check_strang_kernel() {
   }
 }
 
+// The FP32 midpoint kernel of two terms holds 1/3 itself: no angle may ask it for another value.
+void check_two_terms() {
+  int two = 0;
+  for (double x = 1e-6; x < 1e-2; x *= 1.01) {
+    const pdx::TanPolynomial t = pdx::tan_polynomial(x, PD_FP32);
+    if (t.terms != 2) continue;
+    ++two;
+    expect(t.c[2] == pdx::tan_series_coef(2), "two FP32 terms are the series' own");
+    expect(pdx::tan_series_coef(3) * x * x <= 0x1p-27, "two FP32 terms hold to 2^-27");
+  }
+  expect(two > 100, "small angles take two FP32 terms");
+}
+
 int main() {
+  check_two_terms();
   check_failed_allocations();
   check_slots();
   check_kept_memory();
