@@ -233,7 +233,8 @@ pd_status pd_rewind(pd_grid g);
 pd_status pd_propagate(pd_grid g, long long max_steps, void* stream);
 
 /* After the last step: sums n(p) into rho with a fixed-order reduction (the
-   result does not depend on the launch shape), optionally copies n(p) to
+   result does not depend on the launch shape; without rho_out nothing is
+   summed), optionally copies n(p) to
    n_out (n_points doubles; device memory if n_out_on_device, else host
    memory, pageable or, for a copy at the full host-link rate, page-locked), and
    writes rho to the host double *rho_out (may be NULL).  When rho_out or a host

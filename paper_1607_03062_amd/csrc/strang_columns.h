@@ -20,10 +20,10 @@
 //
 // Measured against the row kernel on one machine, whole calls with the steps around it:
 // 2048^2 x 80000 steps fast FP32 51.6 -> 38.6 ms (this kernel alone 54.9 -> 41.9, before the
-// points per lane followed the launch), 1500 x 2047 x 12000 FP32 8.29 -> 5.99 ms, 1024^2 x 40000
-// FP64 13.2 -> 8.7 ms, fourth order 512^2 x 4000 FP64 4.43 -> 1.28 ms, with a y component 1024^2 x
-// 4000 FP32 8.2 -> 5.6 ms.  Fast FP32 issues 1.56-1.63 VALU instructions of 2 per SIMD
-// quad-cycle.
+// points per lane followed the launch), 1500 x 2047 x 12000 FP32 8.34 -> 5.90 ms, 1024^2 x 40000
+// FP64 13.4 -> 8.7 ms, fourth order 512^2 x 4000 FP64 4.40 -> 1.31 ms, with a y component 1024^2 x
+// 4000 FP32 8.3 -> 5.6 ms.  Fast FP32 issues 1.56-1.63 VALU instructions of 2 per SIMD
+// quad-cycle, PD_FP32 1.68-1.70.
 //
 // The FP32 forms' roundings.  PD_FP32 rounds each component once in every rotation (8
 // instructions for a point's step; the row kernel's three rotations 12).  PD_FP32_FAST: plain
